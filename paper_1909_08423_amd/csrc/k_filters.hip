@@ -38,12 +38,17 @@ __device__ __forceinline__ void load_frag(const TN* x, TN* f) {
   }
 }
 
-// KQ1 = K / 4 (features), KQ2 = DZ / 4 (filter width).
-template <typename TN, int KQ1, int KQ2>
+// KQ1 = K / 4 (features), KQ2 = DZ / 4 (filter width).  JETS = false computes
+// and stores the values w only (one of the three jets): what value-only
+// evaluations and the value-path adjoint read (217 -> 148 us per launch at
+// 4096 walkers of a ten-electron atom in FP32; the jets were two thirds of the
+// products and of the table's bytes).
+template <typename TN, int KQ1, int KQ2, bool JETS>
 __global__ __launch_bounds__(kThreads) void k_filters(Dims d, DevTables t, int64_t nw, const double* __restrict__ r,
                                                       const TN* __restrict__ P, ParamLayout pl, TN* __restrict__ filt,
-                                                      int PT, int n_same, bool bf16) {
+                                                      int PT, int n_same) {
   typedef typename MfmaTile<TN>::acc_t acc_t;
+  constexpr int NJ = JETS ? 3 : 1;
   constexpr int K = 4 * KQ1, DZ = 4 * KQ2, LDK = ld_pad<TN>(K), LDZ = ld_pad<TN>(DZ);
   extern __shared__ __align__(16) char smem[];
   const int ch = blockIdx.y;
@@ -56,8 +61,8 @@ __global__ __launch_bounds__(kThreads) void k_filters(Dims d, DevTables t, int64
   const int rows = (int)min((int64_t)PT, nrows - row0);
   double* dd = reinterpret_cast<double*>(smem);       // [PT] distances
   int64_t* doff = reinterpret_cast<int64_t*>(dd + PT);  // [PT] table offset of each row (layer 0)
-  TN* E = reinterpret_cast<TN*>(doff + PT);           // [3][PT][LDK] feature jets
-  TN* U = E + 3 * PT * LDK;                           // [3][PT][LDZ] ssp jets
+  TN* E = reinterpret_cast<TN*>(doff + PT);           // [NJ][PT][LDK] feature jets
+  TN* U = E + NJ * PT * LDK;                          // [NJ][PT][LDZ] ssp jets
   const int64_t lstride = (int64_t)3 * d.n_pairs * DZ, jstride = (int64_t)d.n_pairs * DZ;
 
   // --- distances (padding rows of a partial tile: 0) ---
@@ -91,14 +96,16 @@ __global__ __launch_bounds__(kThreads) void k_filters(Dims d, DevTables t, int64
   for (int q = threadIdx.x; q < PT * K; q += blockDim.x) {
     int row = q / K, k = q % K;
     if (row >= rows) {  // padding rows: zero features
-      E[(0 * PT + row) * LDK + k] = E[(1 * PT + row) * LDK + k] = E[(2 * PT + row) * LDK + k] = TN(0);
+#pragma unroll
+      for (int jet = 0; jet < NJ; ++jet) E[(jet * PT + row) * LDK + k] = TN(0);
       continue;
     }
     double dv = dd[row];
     double dm = dv - t.feat_mu[k], s = t.feat_sig2inv[k];
     double eg = exp(-dv - dm * dm * s);
-    double g1 = -1.0 - 2.0 * dm * s, g2 = -2.0 * s;
     E[(0 * PT + row) * LDK + k] = (TN)(dv * dv * eg);
+    if constexpr (!JETS) continue;
+    double g1 = -1.0 - 2.0 * dm * s, g2 = -2.0 * s;
     E[(1 * PT + row) * LDK + k] = (TN)((2.0 + dv * g1) * eg);                                  // e'/d
     E[(2 * PT + row) * LDK + k] = (TN)((2.0 + 4.0 * dv * g1 + dv * dv * (g1 * g1 + g2)) * eg);  // e''
   }
@@ -137,24 +144,26 @@ __global__ __launch_bounds__(kThreads) void k_filters(Dims d, DevTables t, int64
       for (int s = 0; s < KQ1; ++s) b[s] = W1[(g * KQ1 + s) * DZ + col];
       const TN b1 = P[Lp.w1b[ch] + col];
       for (int rg = rg0; rg < n_rg; rg += rg_step) {
-        acc_t c[3];
+        acc_t c[NJ];
 #pragma unroll
-        for (int jet = 0; jet < 3; ++jet) {
+        for (int jet = 0; jet < NJ; ++jet) {
           TN a[KQ1];
           load_frag<TN, KQ1>(E + (jet * PT + (rg << 4) + c16) * LDK + g * KQ1, a);
           acc_t z;
 #pragma unroll
           for (int v = 0; v < 4; ++v) z[v] = TN(0);
-          c[jet] = MfmaChain<TN, KQ1>::run(a, b, z, bf16);
+          c[jet] = MfmaChain<TN, KQ1>::run(a, b, z, false);
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int row = (rg << 4) + MfmaTile<TN>::row_of(lane, v);
-          const TN u = c[0][v] + b1, ud = c[1][v], u2 = c[2][v];
-          const TN sg = sigmoid_d(u);
-          const TN up = (TN)dd[row] * ud;
+          const TN u = c[0][v] + b1;
           TN* u0 = U + row * LDZ + col;
           u0[0] = ssp(u);
+          if constexpr (!JETS) continue;
+          const TN ud = c[NJ / 2][v], u2 = c[NJ - 1][v];
+          const TN sg = sigmoid_d(u);
+          const TN up = (TN)dd[row] * ud;
           u0[PT * LDZ] = sg * ud;
           u0[2 * PT * LDZ] = sg * u2 + sg * (TN(1) - sg) * up * up;
         }
@@ -171,13 +180,13 @@ __global__ __launch_bounds__(kThreads) void k_filters(Dims d, DevTables t, int64
       const TN b2 = P[Lp.w2b[ch] + col];
       for (int rg = rg0; rg < n_rg; rg += rg_step) {
 #pragma unroll
-        for (int jet = 0; jet < 3; ++jet) {
+        for (int jet = 0; jet < NJ; ++jet) {
           TN a[KQ2];
           load_frag<TN, KQ2>(U + (jet * PT + (rg << 4) + c16) * LDZ + g * KQ2, a);
           acc_t c;
 #pragma unroll
           for (int v = 0; v < 4; ++v) c[v] = TN(0);
-          c = MfmaChain<TN, KQ2>::run(a, b, c, bf16);
+          c = MfmaChain<TN, KQ2>::run(a, b, c, false);
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
             const int row = (rg << 4) + MfmaTile<TN>::row_of(lane, v);
@@ -195,15 +204,15 @@ __global__ __launch_bounds__(kThreads) void k_filters(Dims d, DevTables t, int64
 }  // namespace
 
 template <typename TN>
-size_t filter_lds_bytes(const Dims& d, int PT) {
-  return PT * (sizeof(double) + sizeof(int64_t)) + (size_t)3 * PT * (ld_pad<TN>(d.K) + ld_pad<TN>(d.DZ)) * sizeof(TN);
+size_t filter_lds_bytes(const Dims& d, int PT, bool jets) {
+  return PT * (sizeof(double) + sizeof(int64_t)) + (size_t)(jets ? 3 : 1) * PT * (ld_pad<TN>(d.K) + ld_pad<TN>(d.DZ)) * sizeof(TN);
 }
-template size_t filter_lds_bytes<double>(const Dims&, int);
-template size_t filter_lds_bytes<float>(const Dims&, int);
+template size_t filter_lds_bytes<double>(const Dims&, int, bool);
+template size_t filter_lds_bytes<float>(const Dims&, int, bool);
 
 template <typename TN>
 void launch_filters(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r, const TN* P, char* ws,
-                    const WsLayout& L, bool bf16) {
+                    const WsLayout& L, bool jets) {
   const Dims& d = c->d;
   const int PT = L.filt_rows;
   int n_same = 0;
@@ -211,12 +220,14 @@ void launch_filters(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r,
   n_same = d.n_up * (d.n_up - 1) / 2 + d.n_dn * (d.n_dn - 1) / 2;
   int64_t max_np = std::max<int64_t>(std::max(n_same, d.n_ee - n_same), (int64_t)d.N * d.NN);
   int64_t nbx = (nw * max_np + PT - 1) / PT;
-  size_t lds = filter_lds_bytes<TN>(d, PT);
+  const size_t lds = filter_lds_bytes<TN>(d, PT, jets);
   const dim3 grid((unsigned)nbx, 3), block(kThreads);
   TN* filt = reinterpret_cast<TN*>(ws + L.filt);
-#define PN_FILT(KQ1, KQ2)                                                                                         \
-  hipLaunchKernelGGL((k_filters<TN, KQ1, KQ2>), grid, block, lds, s, d, c->t, nw, r, P, c->pl, filt, PT, n_same, \
-                     bf16)
+#define PN_FILT(KQ1, KQ2)                                                                                     \
+  do {                                                                                                        \
+    auto kern = jets ? &k_filters<TN, KQ1, KQ2, true> : &k_filters<TN, KQ1, KQ2, false>;                      \
+    hipLaunchKernelGGL(kern, grid, block, lds, s, d, c->t, nw, r, P, c->pl, filt, PT, n_same);                \
+  } while (0)
 #define PN_FILT_Z(KQ1)          \
   switch (d.DZ) {               \
     case 16: PN_FILT(KQ1, 4); break;  \

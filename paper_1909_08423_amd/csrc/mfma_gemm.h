@@ -319,17 +319,22 @@ __device__ __forceinline__ void gemm_mfma_k(const TN* X, int ldx, int rows, cons
 // Narrow output: W is [I][ncol] (row stride ncol), the product is computed
 // on ceil(ncol / 16) column tiles and only the ncol valid columns are
 // stored (used for the backflow output layer, ncol = number of orbitals).
-template <typename TN>
+// An own-store epilogue sees every column of the tiles and tests its own.
+template <typename TN, typename EPI = NoEpi>
 __device__ __forceinline__ void gemm_mfma_cols(const TN* X, int ldx, int rows, int I, const TN* __restrict__ W,
-                                               int ncol, TN* Y, int ldy, bool accumulate, bool bf16) {
+                                               int ncol, TN* Y, int ldy, bool accumulate, bool bf16, EPI epi = EPI()) {
   const int O = (ncol + 15) & ~15;
+  auto run = [&](auto kq, const TN* x, const TN* w, bool acc, auto e) {
+    gemm_mfma_k<TN, decltype(kq)::value, false, false, false, false, decltype(e)>(x, ldx, rows, w, ncol, O, ncol, Y, ldy,
+                                                                                acc, bf16, 0, 0, nullptr, 0, nullptr, e);
+  };
   switch (I) {
-    case 16: gemm_mfma_k<TN, 4>(X, ldx, rows, W, ncol, O, ncol, Y, ldy, accumulate, bf16); break;
-    case 32: gemm_mfma_k<TN, 8>(X, ldx, rows, W, ncol, O, ncol, Y, ldy, accumulate, bf16); break;
-    case 64: gemm_mfma_k<TN, 16>(X, ldx, rows, W, ncol, O, ncol, Y, ldy, accumulate, bf16); break;
-    default:
-      gemm_mfma_k<TN, 16>(X, ldx, rows, W, ncol, O, ncol, Y, ldy, accumulate, bf16);
-      gemm_mfma_k<TN, 16>(X + 64, ldx, rows, W + (size_t)64 * ncol, ncol, O, ncol, Y, ldy, true, bf16);
+    case 16: run(std::integral_constant<int, 4>(), X, W, accumulate, epi); break;
+    case 32: run(std::integral_constant<int, 8>(), X, W, accumulate, epi); break;
+    case 64: run(std::integral_constant<int, 16>(), X, W, accumulate, epi); break;
+    default:  // two halves through Y (whose rows are as wide as the column tiles); the epilogue acts on their sum
+      run(std::integral_constant<int, 16>(), X, W, accumulate, NoEpi());
+      run(std::integral_constant<int, 16>(), X + 64, W + (size_t)64 * ncol, true, epi);
       break;
   }
 }

@@ -19,7 +19,7 @@ template <typename TN>
 size_t value_lds_bytes(const Dims& d, int wpb);
 size_t slater_tangent_lds_bytes(const Dims& d, int T);
 template <typename TN>
-size_t filter_lds_bytes(const Dims& d, int PT);
+size_t filter_lds_bytes(const Dims& d, int PT, bool jets);
 bool tangent_chunk_supported(int T);
 void launch_backward(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r, const void* P, bool fp32,
                      bool bf16, const double* ct, char* ws, const WsLayout& L, double* grad_params, bool full);
@@ -219,18 +219,13 @@ WsLayout plan(const pn_ctx* c, int64_t nw, pn_precision prec, int mode, size_t b
   // a block that takes more than half the CU's LDS runs alone on it: 512
   // threads keep two waves per SIMD (chunks of at most 6 coordinates)
   L.tan_threads = (L.lds_tangent > kLdsMax / 2 && L.T <= 6) ? 512 : 256;
-  L.wpb_value = std::max(1, 64 / d.N);
-  while (L.wpb_value > 1 &&
-         (fp64 ? value_lds_bytes<double>(d, L.wpb_value) : value_lds_bytes<float>(d, L.wpb_value)) > 64 * 1024)
-    L.wpb_value /= 2;
-  L.lds_value = fp64 ? value_lds_bytes<double>(d, L.wpb_value) : value_lds_bytes<float>(d, L.wpb_value);
   // 32 pair rows per filter block (measured: 64 rows, two blocks per CU, are
   // 20 % slower in FP32), halved while the tile exceeds 64 KB of LDS
   L.filt_rows = 32;
   while (L.filt_rows > 16 &&
-         (fp64 ? filter_lds_bytes<double>(d, L.filt_rows) : filter_lds_bytes<float>(d, L.filt_rows)) > 64 * 1024)
+         (fp64 ? filter_lds_bytes<double>(d, L.filt_rows, true) : filter_lds_bytes<float>(d, L.filt_rows, true)) > 64 * 1024)
     L.filt_rows /= 2;
-  L.lds_filter = fp64 ? filter_lds_bytes<double>(d, L.filt_rows) : filter_lds_bytes<float>(d, L.filt_rows);
+  L.lds_filter = fp64 ? filter_lds_bytes<double>(d, L.filt_rows, true) : filter_lds_bytes<float>(d, L.filt_rows, true);
   // determinants of the forward pass through one LU per spin when the
   // expansion allows it (and the caller did not ask for the direct path)
   L.lowrank = (mode == kPlanForward || mode == kPlanValueOnly) && d.lr && !(d.flags & PN_DET_DIRECT);
@@ -274,6 +269,29 @@ WsLayout plan(const pn_ctx* c, int64_t nw, pn_precision prec, int mode, size_t b
   int64_t tile = std::max<int64_t>(min_tile, (int64_t)(avail / std::max<size_t>(pw, 1)));
   tile = std::min<int64_t>(tile, std::max<int64_t>(nw, 1));
   L.tile = tile;
+  // Walkers per block of the value pass (at most about 64 rows): the fewest
+  // rounds of resident blocks times a block's time, which is its phases'
+  // latency (about as long as 32 rows) plus its rows in whole MFMA tiles.
+  // At 4096 walkers of ten electrons 6 per block are 683 blocks for 512
+  // places (two rounds, the second a third full), 3 per block are two full
+  // rounds of 768.  At 512 walkers of two electrons 32 per block would leave
+  // 240 CUs idle.
+  {
+    auto lds_value = [&](int wpb) { return fp64 ? value_lds_bytes<double>(d, wpb) : value_lds_bytes<float>(d, wpb); };
+    int64_t best = 0;
+    L.wpb_value = 1;
+    for (int wpb = 1; wpb * d.N <= std::max(64, d.N); ++wpb) {
+      const size_t lds = lds_value(wpb);
+      if (wpb > 1 && lds > 64 * 1024) break;
+      const int64_t places = 256 * std::max<int64_t>(1, std::min<int64_t>(fp64 ? 2 : 3, kLdsMax / lds));
+      const int64_t blocks = (tile + wpb - 1) / wpb, cost = (blocks + places - 1) / places * (32 + (wpb * d.N + 15) / 16 * 16);
+      if (wpb == 1 || cost < best) {
+        best = cost;
+        L.wpb_value = wpb;
+      }
+    }
+    L.lds_value = lds_value(L.wpb_value);
+  }
   size_t off = 0;
   auto region = [&](size_t bytes) {
     size_t o = off;
@@ -880,17 +898,17 @@ pn_status eval_impl(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r,
       launch_fill(s, n, reinterpret_cast<double*>(base + L.jval), 0.0);
     } else if (fp64) {
       clk.begin(2);
-      launch_filters<double>(c, s, n, rt, static_cast<const double*>(P), base, L, false);
+      launch_filters<double>(c, s, n, rt, static_cast<const double*>(P), base, L, derivs);
       clk.end(2);
       clk.begin(3);
-      launch_net_value<double>(c, s, n, static_cast<const double*>(P), base, L, false);
+      launch_net_value<double>(c, s, n, static_cast<const double*>(P), base, L);
       clk.end(3);
     } else {
       clk.begin(2);
-      launch_filters<float>(c, s, n, rt, static_cast<const float*>(P), base, L, false);
+      launch_filters<float>(c, s, n, rt, static_cast<const float*>(P), base, L, derivs);
       clk.end(2);
       clk.begin(3);
-      launch_net_value<float>(c, s, n, static_cast<const float*>(P), base, L, false);
+      launch_net_value<float>(c, s, n, static_cast<const float*>(P), base, L);
       clk.end(3);
     }
     clk.begin(4);
@@ -963,11 +981,11 @@ pn_status pn_eval_backward(const pn_ctx* c, hipStream_t s, int64_t nw, const dou
     const double* rt = r + w0 * d.N * 3;
     launch_geometry_orbitals(c, s, n, rt, base, L);
     if (fp64) {
-      launch_filters<double>(c, s, n, rt, static_cast<const double*>(P), base, L, false);
-      launch_net_value<double>(c, s, n, static_cast<const double*>(P), base, L, false);
+      launch_filters<double>(c, s, n, rt, static_cast<const double*>(P), base, L, full);
+      launch_net_value<double>(c, s, n, static_cast<const double*>(P), base, L);
     } else {
-      launch_filters<float>(c, s, n, rt, static_cast<const float*>(P), base, L, false);
-      launch_net_value<float>(c, s, n, static_cast<const float*>(P), base, L, false);
+      launch_filters<float>(c, s, n, rt, static_cast<const float*>(P), base, L, full);
+      launch_net_value<float>(c, s, n, static_cast<const float*>(P), base, L);
     }
     launch_slater_value(c, s, n, base, L, la, sg);
     const double* ctl = ct_logabs ? ct_logabs + w0 : nullptr;
@@ -1030,10 +1048,10 @@ pn_status pn_eval_backward_cusp(const pn_ctx* c, hipStream_t s, int64_t nw, cons
       launch_fill(s, n, reinterpret_cast<double*>(base + L.jval), 0.0);
     } else if (fp64) {
       launch_filters<double>(c, s, n, rt, static_cast<const double*>(P), base, L, false);
-      launch_net_value<double>(c, s, n, static_cast<const double*>(P), base, L, false);
+      launch_net_value<double>(c, s, n, static_cast<const double*>(P), base, L);
     } else {
       launch_filters<float>(c, s, n, rt, static_cast<const float*>(P), base, L, false);
-      launch_net_value<float>(c, s, n, static_cast<const float*>(P), base, L, false);
+      launch_net_value<float>(c, s, n, static_cast<const float*>(P), base, L);
     }
     launch_slater_value(c, s, n, base, L, la, sg);
     launch_cusp_grad(c, s, n, rt, base, L, ct_logabs + w0, slot, grad_cusp);

@@ -199,6 +199,18 @@ __device__ __forceinline__ float ssp(float x) {
   return (x > 0.f ? x + log1pf(__expf(-x)) : log1pf(__expf(x))) - 0.69314718f;
 }
 
+// Index arithmetic without divisions (a division by a run-time value is some
+// 25 vector instructions): widths are powers of two, and a row index below
+// 2^14 is divided by N <= 64 through the reciprocal ceil(2^20 / N), whose
+// product with it stays below 2^31 and is off by less than 1 / N.
+struct RowDiv {
+  int N, m;
+  __device__ explicit RowDiv(int n) : N(n), m(((1 << 20) + n - 1) / n) {}
+  __device__ int div(int row) const { return (int)(((unsigned)row * (unsigned)m) >> 20); }
+  __device__ int mod(int row) const { return row - div(row) * N; }
+};
+__device__ __forceinline__ int log2_of(int pow2) { return 31 - __builtin_clz((unsigned)pow2); }
+
 // LDS row stride with 16 bytes of padding (keeps 16-byte alignment, spreads
 // rows over the banks).
 template <typename T>
@@ -214,10 +226,9 @@ void launch_geometry_orbitals(const pn_ctx* c, hipStream_t s, int64_t nw, const 
                               const WsLayout& L);
 template <typename TN>
 void launch_filters(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r, const TN* P, char* ws,
-                    const WsLayout& L, bool bf16);
+                    const WsLayout& L, bool jets);
 template <typename TN>
-void launch_net_value(const pn_ctx* c, hipStream_t s, int64_t nw, const TN* P, char* ws, const WsLayout& L,
-                      bool bf16);
+void launch_net_value(const pn_ctx* c, hipStream_t s, int64_t nw, const TN* P, char* ws, const WsLayout& L);
 template <typename TN>
 void launch_net_tangent(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r, const TN* P, char* ws,
                         const WsLayout& L, bool bf16, TN* xsave = nullptr);
