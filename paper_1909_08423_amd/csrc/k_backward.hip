@@ -12,317 +12,491 @@
 // layers (messages, h and the three g) and finally the filter networks.
 //
 // Kernels (the forward values come from the value pass, run just before):
-//  k_bwd_net     groups of WB walkers; grid-stride over groups with a fixed
-//                grid, each block summing its parameter gradients into its
-//                own slot; writes the cotangents of the filter outputs.
+//  k_bwd_net     groups of WB walkers: the reverse sweep.  Leaves both row
+//                tables of every weight gradient, the sums of the bias-like
+//                parameters of its group, and the filter outputs' cotangents.
+//  k_wgrad       (wgrad.h) weight gradients from the row tables, k_wgrad_small
+//                those of the last backflow layer and the bias-like ones; each
+//                into the gradient slot of its group (slot = group mod 512).
 //  k_bwd_filter  per (layer, channel) and a fixed set of blocks striding
 //                over (walker, pair) rows; recomputes features and the
 //                hidden layer, accumulates the filter gradients in registers.
 //  k_bwd_reduce  sums the slots in a fixed order into the FP64 gradient.
-// The fixed grids and slot order make the result independent of anything
+// The fixed groups and slot order make the result independent of anything
 // else running on the device.
 #include "adj_util.h"
 #include "gemm_lds.h"
 #include "mfma_gemm.h"
 #include "pn_internal.h"
+#include "wgrad.h"
 
 namespace pn {
 namespace {
 
-constexpr int kSlotsNet = 512;     // blocks (and gradient slots) of k_bwd_net
+constexpr int kSlotsNet = 512;     // gradient slots of the network weights
 constexpr int kSlotsFilter = 256;  // blocks per (layer, channel) of k_bwd_filter
 constexpr int kFiltRows = 32;      // (walker, pair) rows per tile of k_bwd_filter
 
+// What k_bwd_net leaves behind for the weight gradients ([walker][row]
+// tables, contiguous over the walkers of a launch) and, per group of walkers,
+// the sums of the parameters that are no matrix: offsets into one block.
 template <typename TN>
-__global__ __launch_bounds__(kThreads) void k_bwd_net(Dims d, DevTables t, int64_t nw, int WB,
-                                                      const TN* __restrict__ P, ParamLayout pl,
-                                                      const TN* __restrict__ xval, const TN* __restrict__ hval,
-                                                      const TN* __restrict__ filt, const double* __restrict__ phi,
-                                                      const double* __restrict__ ginv, const double* __restrict__ wdet,
-                                                      const double* __restrict__ ct_logabs, TN* __restrict__ ctw,
-                                                      TN* __restrict__ gslot, int64_t n_params,
-                                                      const double* __restrict__ ctfpart, int n_chunks,
-                                                      const TN* __restrict__ cthv, const TN* __restrict__ ctkc,
-                                                      const TN* __restrict__ ctec, TN* __restrict__ arena,
-                                                      int64_t arena_elems) {
+struct NetOps {
+  TN *z, *cx, *ch;             // [L][3][nw N][DZ] messages, [L][nw N][DX] cotangents of x^(n+1), [L][nw N][DZ] of h
+  TN *a1, *c2, *c1, *a2, *cf;  // backflow head: [nw N][DX] activations and cotangents, [nw N][M] cotangent of f
+  TN *s, *e1, *ec1, *ec2;      // Jastrow head: [nw][DX]
+  TN* small;                   // [groups][SmallSums::total]
+};
+
+struct SmallSums {
+  int eW3, eb3, eb2, eb1, kb3, kb2, kb1, x0, layer, gb, hb, Y, step, total;  // layer n at layer + n step + gb | hb | Y
+  __host__ __device__ explicit SmallSums(const Dims& d) {
+    int o = 0;
+    auto take = [&](int n) {
+      const int at = o;
+      o += n;
+      return at;
+    };
+    eW3 = take(d.DX), eb3 = take(1), eb2 = take(d.DX), eb1 = take(d.DX);
+    kb3 = take(d.M), kb2 = take(d.DX), kb1 = take(d.DX), x0 = take(d.DX);
+    layer = o;
+    gb = 0, hb = d.DX, Y = hb + d.DZ, step = Y + d.NN * d.DZ;
+    total = layer + d.L * step;
+  }
+};
+
+// out[b] = sum_r Y[r][b]
+template <typename TN>
+__device__ __forceinline__ void colsum(const TN* Y, int ldy, int B, int rows, TN* out) {
+  for (int b = threadIdx.x; b < B; b += blockDim.x) {
+    TN s = 0;
+    for (int r = 0; r < rows; ++r) s += Y[r * ldy + b];
+    out[b] = s;
+  }
+}
+
+// The sweep's products are small (a group has some tens of rows), so its time
+// is latency: of the barriers, of the filter values (each read once, for the
+// message and for the cotangent of h together, eight partners at a time), and
+// of the index arithmetic.  The weight gradients, which would read and write
+// every parameter of a slot once per group, are left to k_wgrad.
+// Measured per launch (FP32): 14.2 -> 2.9 ms (+ 0.5 ms of weight gradients) at
+// 2048 walkers of the 30-electron diatomic, 1.44 -> 0.57 ms at 4096 walkers of
+// a ten-electron atom, against one kernel that added every group's weight
+// gradients to slots in memory and took the channels one after the other.
+template <typename TN, int NT>
+__global__ __launch_bounds__(NT, 512 / NT) void k_bwd_net(Dims d, DevTables t, int64_t nw, int WB,
+                                                          const TN* __restrict__ P, ParamLayout pl,
+                                                          const TN* __restrict__ xval, const TN* __restrict__ hval,
+                                                          const TN* __restrict__ filt, const double* __restrict__ phi,
+                                                          const double* __restrict__ ginv,
+                                                          const double* __restrict__ wdet,
+                                                          const double* __restrict__ ct_logabs, TN* __restrict__ ctw,
+                                                          const double* __restrict__ ctfpart, int n_chunks,
+                                                          const TN* __restrict__ cthv, const TN* __restrict__ ctkc,
+                                                          const TN* __restrict__ ctec, NetOps<TN> op,
+                                                          TN* __restrict__ arena, int64_t arena_elems) {
   extern __shared__ __align__(16) char smem[];
-  const int N = d.N, DX = d.DX, DZ = d.DZ, M = d.M, L = d.L, NU = d.n_up;
+  const int N = d.N, DX = d.DX, DZ = d.DZ, M = d.M, L = d.L, NU = d.n_up, P2 = 2 * d.P;
   const int LDX = ld_pad<TN>(DX), LDZ = ld_pad<TN>(DZ), LDM = ld_pad<TN>((M + 15) & ~15);
   const int RW = WB * N;
-  TN* slot = gslot + (size_t)blockIdx.x * n_params;
-  int* pidx = reinterpret_cast<int*>(smem);
-  TN* cw = reinterpret_cast<TN*>(pidx + ((N * N + 3) & ~3));  // [WB]
-  TN* X = cw + ((WB + 3) & ~3);                                 // [RW][LDX]
-  TN* CX = X + RW * LDX;                                        // [RW][LDX]
+  const int sx = log2_of(DX), sz = log2_of(DZ);
+  const RowDiv rN(N);
+  const SmallSums sm(d);
+  int* pidx = reinterpret_cast<int*>(smem);                              // [N][N]
+  unsigned short* pij = reinterpret_cast<unsigned short*>(pidx + ((N * N + 3) & ~3));  // [n_ee] i + 256 j
+  signed char* inv = reinterpret_cast<signed char*>(pij + ((d.n_ee + 7) & ~7));  // [P][2][M] slot of an orbital
+  TN* cw = reinterpret_cast<TN*>(inv + ((P2 * M + 15) & ~15));           // [WB]
+  TN* CX = cw + ((WB + 3) & ~3);                                         // [RW][LDX]
   // union region (heads, then layers): in LDS, or in this block's part of a
-  // global arena when it does not fit beside X and CX
+  // global arena when it does not fit beside CX
   TN* UN = arena ? arena + (size_t)blockIdx.x * arena_elems : CX + RW * LDX;
   // heads view
-  TN* A = UN;                  // [RW][LDX]
-  TN* B = A + RW * LDX;        // [RW][LDX]
-  TN* Cb = B + RW * LDX;       // [RW][LDX]
-  TN* CF = Cb + RW * LDX;      // [RW][LDM]
+  TN* X = UN;                  // [RW][LDX] x^(L), then the second pre-activation and its product
+  TN* A = X + RW * LDX;        // [RW][LDX] first pre-activation
+  TN* B = A + RW * LDX;        // [RW][LDX] first activation, then the second's cotangent
+  TN* CF = B + RW * LDX;       // [RW][LDM] cotangent of f
+  TN* Sv = CF + RW * LDM;      // [WB][LDX] sum_i x_i
+  TN* U1 = Sv + WB * LDX;      // pre-activations of the Jastrow head
+  TN* U2 = U1 + WB * LDX;
+  TN* Y1 = U2 + WB * LDX;
+  TN* C1 = Y1 + WB * LDX;      // cotangents
+  TN* C2 = C1 + WB * LDX;
   // layers view
   TN* H = UN;                  // [RW][LDZ]
-  TN* Z = H + RW * LDZ;
-  TN* CZ = Z + RW * LDZ;
-  TN* CH = CZ + RW * LDZ;
+  TN* CZ = H + RW * LDZ;       // [3][RW][LDZ]
+  TN* CH = CZ + 3 * RW * LDZ;  // [RW][LDZ]
   const int64_t fl_stride = (int64_t)3 * d.n_pairs * DZ;
   const int64_t ng = (nw + WB - 1) / WB;
+  const int n_same = (d.n_up * (d.n_up - 1) + d.n_dn * (d.n_dn - 1)) / 2;
+  const TN jas = (d.flags & PN_NET_NO_JASTROW) ? TN(0) : TN(1);  // a removed Jastrow factor gets no cotangent
   for (int q = threadIdx.x; q < N * N; q += blockDim.x) pidx[q] = t.pair_index[q];
-  bool first = true;
-  for (int64_t grp = blockIdx.x; grp < ng; grp += gridDim.x, first = false) {
-    const int64_t w0 = grp * WB;
+  for (int q = threadIdx.x; q < d.n_ee; q += blockDim.x)
+    pij[q] = (unsigned short)(t.pair_ij[2 * q] + 256 * t.pair_ij[2 * q + 1]);
+  for (int q = threadIdx.x; q < P2 * M; q += blockDim.x) inv[q] = -1;
+  __syncthreads();
+  for (int q = threadIdx.x; q < d.P * N; q += blockDim.x) {
+    const int p = q / N, k = q % N;
+    const bool up = k < NU;
+    inv[(2 * p + !up) * M + (up ? t.det_up[p * d.n_up + k] : t.det_dn[p * d.n_dn + k - NU])] =
+        (signed char)(up ? k : k - NU);
+  }
+  for (int64_t grp = blockIdx.x; grp < ng; grp += gridDim.x) {
+    const int64_t w0 = grp * WB, row0 = w0 * N;
     const int nwb = (int)min((int64_t)WB, nw - w0);
     const int R = nwb * N;
+    TN* small = op.small + grp * sm.total;
     __syncthreads();
     for (int q = threadIdx.x; q < nwb; q += blockDim.x) cw[q] = (TN)ct_logabs[w0 + q];
-    const TN jas = (d.flags & PN_NET_NO_JASTROW) ? TN(0) : TN(1);  // a removed Jastrow factor gets no cotangent
-    // ---- cotangent of the backflow, from the determinants ----
-    for (int q = threadIdx.x; q < R * LDM; q += blockDim.x) CF[q] = 0;
-    for (int q = threadIdx.x; q < R * DX; q += blockDim.x)
-      X[(q / DX) * LDX + q % DX] = xval[((w0 + q / (N * DX)) * (L + 1) + L) * N * DX + q % (N * DX)];
+    const TN* xl = xval + ((int64_t)L * nw * N + row0) * DX;
+    for (int q = threadIdx.x; q < R * DX; q += blockDim.x) X[(q >> sx) * LDX + (q & (DX - 1))] = xl[q];
     __syncthreads();
+    // ---- cotangent of the backflow, from the determinants; the sum of the
+    // embeddings; the first products of both heads ----
     const int gsz = d.n_up * d.n_up + d.n_dn * d.n_dn;
-    for (int row = threadIdx.x; row < R; row += blockDim.x) {
-      const int wl = row / N, i = row % N;
+    for (int q = threadIdx.x; q < R * LDM; q += blockDim.x) {
+      const int row = q / LDM, mu = q - row * LDM, wl = rN.div(row), i = row - wl * N;
       const int64_t w = w0 + wl;
-      const bool up = i < NU;
-      const int n = up ? d.n_up : d.n_dn, ii = up ? i : i - NU;
-      const int* dets = up ? t.det_up : t.det_dn;
-      for (int p = 0; p < d.P; ++p) {
-        const double wp = wdet[w * d.P + p];
-        const double* G = ginv + (w * d.P + p) * gsz + (up ? 0 : d.n_up * d.n_up);
-        for (int k = 0; k < n; ++k) CF[row * LDM + dets[p * n + k]] += (TN)(wp * G[ii * n + k]);
-      }
-      const double* ph = phi + (w * N + i) * M * 7;
-      if (d.flags & PN_NET_NO_BACKFLOW) {
-        for (int mu = 0; mu < M; ++mu) CF[row * LDM + mu] = 0;  // f = 1 does not depend on theta
-      } else if (ctfpart) {
-        // full adjoint: the determinant part supplies the cotangent of f
-        // (its ln|psi| share included), summed over the coordinate chunks
-        for (int mu = 0; mu < M; ++mu) {
+      TN cf = 0;
+      if (mu < M && !(d.flags & PN_NET_NO_BACKFLOW)) {  // f = 1 does not depend on theta
+        if (ctfpart) {
+          // full adjoint: the determinant part supplies the cotangent of f
+          // (its ln|psi| share included), summed over the coordinate chunks
           double v = 0.0;
           for (int c = 0; c < n_chunks; ++c) v += ctfpart[((w * n_chunks + c) * N + i) * M + mu];
-          CF[row * LDM + mu] = (TN)v;
+          cf = (TN)v;
+        } else {
+          const bool up = i < NU;
+          const int n = up ? d.n_up : d.n_dn, ii = up ? i : i - NU;
+          const double* G = ginv + w * d.P * gsz + (up ? 0 : d.n_up * d.n_up) + ii * n;
+          const double* wd = wdet + w * d.P;
+          for (int p = 0; p < d.P; p += 4) {
+            double gv[4], wv[4];
+            int kk[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const int pu = min(p + u, d.P - 1);
+              kk[u] = p + u < d.P ? inv[(2 * pu + !up) * M + mu] : -1;
+              gv[u] = G[(int64_t)pu * gsz + max(kk[u], 0)];
+              wv[u] = wd[pu];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (kk[u] >= 0) cf += (TN)(wv[u] * gv[u]);
+          }
+          cf *= (TN)(phi[((w * N + i) * M + mu) * 7]) * cw[wl];
         }
-      } else {
-        for (int mu = 0; mu < M; ++mu) CF[row * LDM + mu] *= (TN)(ph[mu * 7]) * cw[wl];
+      }
+      CF[q] = cf;
+      if (mu < M) op.cf[(row0 + row) * M + mu] = cf;
+    }
+    for (int q = threadIdx.x; q < nwb * DX; q += blockDim.x) {
+      const int wl = q >> sx, x = q & (DX - 1);
+      TN s = 0;
+      for (int i = 0; i < N; ++i) s += X[(wl * N + i) * LDX + x];
+      Sv[wl * LDX + x] = s;
+      op.s[w0 * DX + q] = s;
+    }
+    gemm_mfma<TN>(X, LDX, R, DX, P + pl.kW1, DX, A, LDX, false, false);
+    __syncthreads();
+    gemm_mfma<TN>(Sv, LDX, nwb, DX, P + pl.eW1, DX, U1, LDX, false, false);
+    for (int q = threadIdx.x; q < R * DX; q += blockDim.x) {
+      const int o = (q >> sx) * LDX + (q & (DX - 1));
+      const TN u1 = A[o] + P[pl.kb1 + (q & (DX - 1))];
+      const TN y = ssp(u1);
+      A[o] = u1;
+      B[o] = y;
+      op.a1[row0 * DX + q] = y;
+    }
+    colsum<TN>(CF, LDM, M, R, small + sm.kb3);
+    __syncthreads();
+    for (int q = threadIdx.x; q < nwb * DX; q += blockDim.x) {
+      const int o = (q >> sx) * LDX + (q & (DX - 1));
+      const TN u1 = U1[o] + P[pl.eb1 + (q & (DX - 1))];
+      const TN y = ssp(u1);
+      U1[o] = u1;
+      Y1[o] = y;
+      op.e1[w0 * DX + q] = y;
+    }
+    gemm_mfma<TN>(B, LDX, R, DX, P + pl.kW2, DX, X, LDX, false, false);
+    __syncthreads();
+    gemm_mfma<TN>(Y1, LDX, nwb, DX, P + pl.eW2, DX, U2, LDX, false, false);
+    // d/d y2 = CF W3^T (W3 is [DX][M]), eight rows per read of W3; then d/d u2
+    for (int q = threadIdx.x; q < ((R + 7) >> 3) * DX; q += blockDim.x) {
+      const int x = q & (DX - 1), r0 = (q >> sx) * 8, nr = min(8, R - r0);
+      const TN* w3 = P + pl.kW3 + x * M;
+      TN sv[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) sv[k] = 0;
+      for (int mu = 0; mu < M; ++mu) {
+        const TN w = w3[mu];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) sv[k] += CF[min(r0 + k, R - 1) * LDM + mu] * w;
+      }
+      const TN b2 = P[pl.kb2 + x];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        if (k >= nr) break;
+        const int r = r0 + k;
+        const TN u2 = X[r * LDX + x] + b2;
+        TN c2 = sv[k] * sig(u2);  // d/d u2
+        if (ctkc) {
+          const int wl = rN.div(r);
+          const TN* ck = ctkc + ((w0 + wl) * 4 + 2) * N * DX + (r - wl * N) * DX + x;
+          c2 += ck[0] * ssp2(u2) + ck[N * DX] * ssp3(u2);
+        }
+        B[r * LDX + x] = c2;
+        op.a2[(row0 + r) * DX + x] = ssp(u2);
+        op.c2[(row0 + r) * DX + x] = c2;
       }
     }
     __syncthreads();
-    // ---- Jastrow head (per walker): J = eta(sum_i x_i) ----
-    {
-      TN* Sv = CF + RW * LDM;  // [WB][LDX] s
-      TN* U1 = Sv + WB * LDX;  // pre-activations
-      TN* U2 = U1 + WB * LDX;
-      TN* Y1 = U2 + WB * LDX;
-      TN* C1 = Y1 + WB * LDX;  // cotangents
-      TN* C2 = C1 + WB * LDX;
-      for (int q = threadIdx.x; q < nwb * DX; q += blockDim.x) {
-        const int wl = q / DX, x = q % DX;
-        TN s = 0;
-        for (int i = 0; i < N; ++i) s += X[(wl * N + i) * LDX + x];
-        Sv[wl * LDX + x] = s;
-      }
-      __syncthreads();
-      gemm_mfma<TN>(Sv, LDX, nwb, DX, P + pl.eW1, DX, U1, LDX, false, false);
-      __syncthreads();
-      for (int q = threadIdx.x; q < nwb * DX; q += blockDim.x) {
-        const int r = q / DX, x = q % DX;
-        U1[r * LDX + x] += P[pl.eb1 + x];
-        Y1[r * LDX + x] = ssp(U1[r * LDX + x]);
-      }
-      __syncthreads();
-      gemm_mfma<TN>(Y1, LDX, nwb, DX, P + pl.eW2, DX, U2, LDX, false, false);
-      __syncthreads();
-      for (int q = threadIdx.x; q < nwb * DX; q += blockDim.x) {
-        const int r = q / DX, x = q % DX;
-        U2[r * LDX + x] += P[pl.eb2 + x];
+    for (int x = threadIdx.x; x < DX; x += blockDim.x) {
+      TN s = 0;
+      const TN b2 = P[pl.eb2 + x], w3 = P[pl.eW3 + x];
+      for (int r = 0; r < nwb; ++r) {
         // d/d u2 = cJ * W3[x] * ssp'(u2)
-        const TN u2 = U2[r * LDX + x];
-        TN c2 = jas * cw[r] * P[pl.eW3 + x] * sig(u2);
+        const TN u2 = U2[r * LDX + x] + b2;
+        TN c2 = jas * cw[r] * w3 * sig(u2);
         if (ctec) {  // tangent-pass cotangents of ssp'(u2), ssp''(u2)
           const TN* ce = ctec + ((w0 + r) * 2 + 1) * 2 * DX;
           c2 += ce[x] * ssp2(u2) + ce[DX + x] * ssp3(u2);
         }
         C2[r * LDX + x] = c2;
+        op.ec2[(w0 + r) * DX + x] = c2;
+        s += jas * ssp(u2) * cw[r];
       }
-      __syncthreads();
-      // dW3, db3
-      for (int x = threadIdx.x; x < DX; x += blockDim.x) {
-        TN s = 0;
-        for (int r = 0; r < nwb; ++r) s += jas * ssp(U2[r * LDX + x]) * cw[r];
-        slot[pl.eW3 + x] = first ? s : slot[pl.eW3 + x] + s;
-      }
-      if (threadIdx.x == 0) {
-        TN s = 0;
-        for (int r = 0; r < nwb; ++r) s += jas * cw[r];
-        slot[pl.eb3] = first ? s : slot[pl.eb3] + s;
-      }
-      outer_mfma<TN, true>(U1, LDX, DX, C2, LDX, DX, nwb, slot + pl.eW2, first);
-      colsum_acc<TN>(C2, LDX, DX, nwb, slot + pl.eb2, first);
-      gemm_mfma_wt<TN>(C2, LDX, nwb, DX, P + pl.eW2, DX, C1, LDX, false);
-      __syncthreads();
-      for (int q = threadIdx.x; q < nwb * DX; q += blockDim.x) {
-        const int r = q / DX, x = q % DX;
-        const TN u1 = U1[r * LDX + x];
-        TN c1 = C1[r * LDX + x] * sig(u1);
-        if (ctec) {
-          const TN* ce = ctec + ((w0 + r) * 2 + 0) * 2 * DX;
-          c1 += ce[x] * ssp2(u1) + ce[DX + x] * ssp3(u1);
-        }
-        C1[r * LDX + x] = c1;
-      }
-      __syncthreads();
-      outer_mfma<TN, false>(Sv, LDX, DX, C1, LDX, DX, nwb, slot + pl.eW1, first);
-      colsum_acc<TN>(C1, LDX, DX, nwb, slot + pl.eb1, first);
-      gemm_mfma_wt<TN>(C1, LDX, nwb, DX, P + pl.eW1, DX, C2, LDX, false);  // d/d s
-      __syncthreads();
-      for (int q = threadIdx.x; q < R * DX; q += blockDim.x) {
-        const int row = q / DX, x = q % DX;
-        CX[row * LDX + x] = C2[(row / N) * LDX + x];
-      }
-      __syncthreads();
+      small[sm.eW3 + x] = s;
     }
-    // ---- backflow head: f = 1 + kappa(x_i) ----
-    gemm_mfma<TN>(X, LDX, R, DX, P + pl.kW1, DX, A, LDX, false, false);
-    __syncthreads();
-    for (int q = threadIdx.x; q < R * DX; q += blockDim.x) {
-      const int r = q / DX, x = q % DX;
-      A[r * LDX + x] += P[pl.kb1 + x];
-      B[r * LDX + x] = ssp(A[r * LDX + x]);
-    }
-    __syncthreads();
-    gemm_mfma<TN>(B, LDX, R, DX, P + pl.kW2, DX, Cb, LDX, false, false);
-    __syncthreads();
-    for (int q = threadIdx.x; q < R * DX; q += blockDim.x) Cb[(q / DX) * LDX + q % DX] += P[pl.kb2 + q % DX];
-    __syncthreads();
-    outer_acc_ssp<TN>(Cb, LDX, DX, CF, LDM, M, R, slot + pl.kW3, first);
-    colsum_acc<TN>(CF, LDM, M, R, slot + pl.kb3, first);
-    // d/d y2 = CF W3^T  (W3 is [DX][M]; rows of the transposed product are M long)
-    for (int q = threadIdx.x; q < R * DX; q += blockDim.x) {
-      const int r = q / DX, x = q % DX;
+    if (threadIdx.x == 0) {
       TN s = 0;
-      for (int mu = 0; mu < M; ++mu) s += CF[r * LDM + mu] * P[pl.kW3 + x * M + mu];
-      const TN u2 = Cb[r * LDX + x];
-      TN c2 = s * sig(u2);  // d/d u2
-      if (ctkc) {
-        const int64_t wl = w0 + r / N;
-        const TN* ck = ctkc + (wl * 2 + 1) * 2 * N * DX + (r % N) * DX + x;
-        c2 += ck[0] * ssp2(u2) + ck[N * DX] * ssp3(u2);
-      }
-      B[r * LDX + x] = c2;
+      for (int r = 0; r < nwb; ++r) s += jas * cw[r];
+      small[sm.eb3] = s;
     }
+    gemm_mfma_wt<TN>(B, LDX, R, DX, P + pl.kW2, DX, X, LDX, false);
+    colsum<TN>(B, LDX, DX, R, small + sm.kb2);
     __syncthreads();
-    outer_mfma<TN, true>(A, LDX, DX, B, LDX, DX, R, slot + pl.kW2, first);
-    colsum_acc<TN>(B, LDX, DX, R, slot + pl.kb2, first);
-    gemm_mfma_wt<TN>(B, LDX, R, DX, P + pl.kW2, DX, Cb, LDX, false);
-    __syncthreads();
+    gemm_mfma_wt<TN>(C2, LDX, nwb, DX, P + pl.eW2, DX, C1, LDX, false);
+    colsum<TN>(C2, LDX, DX, nwb, small + sm.eb2);
     for (int q = threadIdx.x; q < R * DX; q += blockDim.x) {
-      const int r = q / DX, x = q % DX;
+      const int r = q >> sx, x = q & (DX - 1);
       const TN u1 = A[r * LDX + x];
-      TN c1 = Cb[r * LDX + x] * sig(u1);  // d/d u1
+      TN c1 = X[r * LDX + x] * sig(u1);  // d/d u1
       if (ctkc) {
-        const int64_t wl = w0 + r / N;
-        const TN* ck = ctkc + (wl * 2 + 0) * 2 * N * DX + (r % N) * DX + x;
+        const int wl = rN.div(r);
+        const TN* ck = ctkc + (w0 + wl) * 4 * N * DX + (r - wl * N) * DX + x;
         c1 += ck[0] * ssp2(u1) + ck[N * DX] * ssp3(u1);
       }
-      Cb[r * LDX + x] = c1;
+      X[r * LDX + x] = c1;
+      op.c1[row0 * DX + q] = c1;
     }
     __syncthreads();
-    outer_mfma<TN, false>(X, LDX, DX, Cb, LDX, DX, R, slot + pl.kW1, first);
-    colsum_acc<TN>(Cb, LDX, DX, R, slot + pl.kb1, first);
-    gemm_mfma_wt<TN>(Cb, LDX, R, DX, P + pl.kW1, DX, CX, LDX, true);
+    for (int q = threadIdx.x; q < nwb * DX; q += blockDim.x) {
+      const int r = q >> sx, x = q & (DX - 1);
+      const TN u1 = U1[r * LDX + x];
+      TN c1 = C1[r * LDX + x] * sig(u1);
+      if (ctec) {
+        const TN* ce = ctec + (w0 + r) * 4 * DX;
+        c1 += ce[x] * ssp2(u1) + ce[DX + x] * ssp3(u1);
+      }
+      C1[r * LDX + x] = c1;
+      op.ec1[w0 * DX + q] = c1;
+    }
+    colsum<TN>(X, LDX, DX, R, small + sm.kb1);
+    __syncthreads();
+    gemm_mfma_wt<TN>(C1, LDX, nwb, DX, P + pl.eW1, DX, C2, LDX, false);  // d/d s
+    colsum<TN>(C1, LDX, DX, nwb, small + sm.eb1);
+    __syncthreads();
+    for (int q = threadIdx.x; q < R * DX; q += blockDim.x) {
+      const int row = q >> sx, x = q & (DX - 1);
+      CX[row * LDX + x] = C2[rN.div(row) * LDX + x];
+    }
+    __syncthreads();
+    gemm_mfma_wt<TN>(X, LDX, R, DX, P + pl.kW1, DX, CX, LDX, true);
     __syncthreads();
     // ---- interaction layers, last to first ----
     for (int n = L - 1; n >= 0; --n) {
       const ParamLayout::Layer& Lp = pl.layer[n];
-      for (int q = threadIdx.x; q < R * DX; q += blockDim.x)
-        X[(q / DX) * LDX + q % DX] = xval[((w0 + q / (N * DX)) * (L + 1) + n) * N * DX + q % (N * DX)];
+      TN* sml = small + sm.layer + n * sm.step;
       for (int q = threadIdx.x; q < R * DZ; q += blockDim.x) {
-        H[(q / DZ) * LDZ + q % DZ] = hval[((w0 + q / (N * DZ)) * L + n) * N * DZ + q % (N * DZ)];
+        const int row = q >> sz, z = q & (DZ - 1), wl = rN.div(row);
+        const int64_t o = (((w0 + wl) * L + n) * N + (row - wl * N)) * DZ + z;
+        H[row * LDZ + z] = hval[o];
         // the tangent pass's cotangent of the h values seeds the h adjoint
-        CH[(q / DZ) * LDZ + q % DZ] = cthv ? cthv[((w0 + q / (N * DZ)) * L + n) * N * DZ + q % (N * DZ)] : TN(0);
+        CH[row * LDZ + z] = cthv ? cthv[o] : TN(0);
+      }
+      {
+        TN* oc = op.cx + ((int64_t)n * nw * N + row0) * DX;
+        for (int q = threadIdx.x; q < R * DX; q += blockDim.x) oc[q] = CX[(q >> sx) * LDX + (q & (DX - 1))];
+      }
+      colsum<TN>(CX, LDX, DX, R, sml + sm.gb);  // the same for the three channels' biases
+      for (int ch = 0; ch < 3; ++ch)            // d/d z
+        gemm_mfma_wt<TN>(CX, LDX, R, DX, P + Lp.gW[ch], DZ, CZ + ch * RW * LDZ, LDZ, false);
+      __syncthreads();
+      // messages z_i = sum_j w_ij h_j (recomputed for the weight gradients)
+      // and d/d h_i += sum_j w_ij d/d z_j, from the same filter values
+      TN* oz = op.z + ((int64_t)n * 3 * nw * N + row0) * DZ;
+      const int64_t oz_ch = nw * N * DZ;
+      for (int q = threadIdx.x; q < R * DZ; q += blockDim.x) {
+        const int row = q >> sz, z = q & (DZ - 1), wl = rN.div(row), i = row - wl * N;
+        const TN* fv = filt + (w0 + wl) * fl_stride * L + n * fl_stride + z;
+        TN chv = CH[row * LDZ + z];
+        for (int ch = 0; ch < 2; ++ch) {
+          const bool want_up = (ch == 0) == (i < NU);
+          const int j_lo = want_up ? 0 : NU, j_hi = want_up ? NU : N;
+          const TN* hz = H + wl * N * LDZ + z;
+          const TN* cz = CZ + (ch * RW + wl * N) * LDZ + z;
+          TN acc = 0, cac = 0;
+          for (int j = j_lo; j < j_hi; j += 8) {
+            TN wv[8], hv[8], cv[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+              const int jj = min(j + k, j_hi - 1);
+              wv[k] = fv[max(pidx[i * N + jj], 0) * DZ];
+              hv[k] = hz[jj * LDZ];
+              cv[k] = cz[jj * LDZ];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+              const bool on = j + k < j_hi && j + k != i;  // else both terms are exact zeros
+              const TN w = on ? wv[k] : TN(0);
+              acc += w * (on ? hv[k] : TN(0));
+              cac += w * (on ? cv[k] : TN(0));
+            }
+          }
+          oz[ch * oz_ch + q] = acc;
+          chv += cac;
+        }
+        CH[row * LDZ + z] = chv;
+        TN acc = 0;
+        for (int I = 0; I < d.NN; ++I) acc += fv[(d.n_ee + i * d.NN + I) * DZ] * P[pl.Y + I * DZ + z];
+        oz[2 * oz_ch + q] = acc;
+      }
+      // cotangents of the filter outputs
+      for (int wl = 0; wl < nwb; ++wl) {
+        TN* cwp = ctw + ((w0 + wl) * L + n) * (int64_t)d.n_pairs * DZ;
+        const TN* hz = H + wl * N * LDZ;
+        for (int q = threadIdx.x; q < d.n_ee * DZ; q += blockDim.x) {
+          const int p = q >> sz, z = q & (DZ - 1), i = pij[p] & 255, j = pij[p] >> 8;
+          const TN* cz = CZ + ((p < n_same ? 0 : RW) + wl * N) * LDZ + z;
+          const TN v = cz[i * LDZ] * hz[j * LDZ + z] + cz[j * LDZ] * hz[i * LDZ + z];
+          cwp[q] = v;
+        }
+        const TN* cn = CZ + (2 * RW + wl * N) * LDZ;
+        for (int q = threadIdx.x; q < N * d.NN * DZ; q += blockDim.x) {
+          const int iI = q >> sz, z = q & (DZ - 1), i = iI / d.NN, I = iI - i * d.NN;
+          cwp[d.n_ee * DZ + q] = cn[i * LDZ + z] * P[pl.Y + I * DZ + z];
+        }
+      }
+      // d/d Y_I = sum over layers and electrons of w_iI d/d z_i (this layer's share)
+      for (int q = threadIdx.x; q < d.NN * DZ; q += blockDim.x) {
+        const int I = q >> sz, z = q & (DZ - 1);
+        TN s = 0;
+        for (int r0 = 0; r0 < R; r0 += 8) {
+          TN fv[8], cv[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            const int row = min(r0 + k, R - 1), wl = rN.div(row), i = row - wl * N;
+            fv[k] = filt[((w0 + wl) * L + n) * fl_stride + (d.n_ee + i * d.NN + I) * DZ + z];
+            cv[k] = CZ[(2 * RW + row) * LDZ + z];
+          }
+#pragma unroll
+          for (int k = 0; k < 8; ++k)
+            if (r0 + k < R) s += fv[k] * cv[k];
+        }
+        sml[sm.Y + q] = s;
       }
       __syncthreads();
-      for (int ch = 0; ch < 3; ++ch) {
-        // recompute the messages of this channel
-        for (int q = threadIdx.x; q < R * DZ; q += blockDim.x) {
-          const int row = q / DZ, z = q % DZ, wl = row / N, i = row % N;
-          const TN* fv = filt + (w0 + wl) * fl_stride * L + n * fl_stride;
-          TN acc = 0;
-          if (ch < 2) {
-            const bool want_up = (ch == 0) == (i < NU);
-            for (int j = want_up ? 0 : NU; j < (want_up ? NU : N); ++j) {
-              if (j == i) continue;
-              acc += fv[(int64_t)pidx[i * N + j] * DZ + z] * H[(wl * N + j) * LDZ + z];
-            }
-          } else {
-            for (int I = 0; I < d.NN; ++I) acc += fv[(int64_t)(d.n_ee + i * d.NN + I) * DZ + z] * P[pl.Y + I * DZ + z];
-          }
-          Z[row * LDZ + z] = acc;
-        }
-        __syncthreads();
-        outer_mfma<TN, false>(Z, LDZ, DZ, CX, LDX, DX, R, slot + Lp.gW[ch], first);
-        colsum_acc<TN>(CX, LDX, DX, R, slot + Lp.gb[ch], first);
-        gemm_mfma_wt<TN>(CX, LDX, R, DX, P + Lp.gW[ch], DZ, CZ, LDZ, false);  // d/d z
-        __syncthreads();
-        if (ch < 2) {
-          // d/d h_j += sum_i w_ij d/d z_i ; filter cotangent per pair
-          for (int q = threadIdx.x; q < R * DZ; q += blockDim.x) {
-            const int row = q / DZ, z = q % DZ, wl = row / N, j = row % N;
-            const TN* fv = filt + (w0 + wl) * fl_stride * L + n * fl_stride;
-            const bool want_up = (ch == 0) == (j < NU);
-            TN acc = 0;
-            for (int i = want_up ? 0 : NU; i < (want_up ? NU : N); ++i) {
-              if (i == j) continue;
-              acc += fv[(int64_t)pidx[i * N + j] * DZ + z] * CZ[(wl * N + i) * LDZ + z];
-            }
-            CH[row * LDZ + z] += acc;
-          }
-          const int p_lo = ch == 0 ? 0 : (d.n_up * (d.n_up - 1) + d.n_dn * (d.n_dn - 1)) / 2;
-          const int p_hi = ch == 0 ? p_lo + (d.n_up * (d.n_up - 1) + d.n_dn * (d.n_dn - 1)) / 2 : d.n_ee;
-          for (int q = threadIdx.x; q < nwb * (p_hi - p_lo) * DZ; q += blockDim.x) {
-            const int wl = q / ((p_hi - p_lo) * DZ), rem = q % ((p_hi - p_lo) * DZ);
-            const int p = p_lo + rem / DZ, z = rem % DZ;
-            const int i = t.pair_ij[2 * p], j = t.pair_ij[2 * p + 1];
-            const TN v = CZ[(wl * N + i) * LDZ + z] * H[(wl * N + j) * LDZ + z] +
-                         CZ[(wl * N + j) * LDZ + z] * H[(wl * N + i) * LDZ + z];
-            ctw[(((w0 + wl) * L + n) * d.n_pairs + p) * DZ + z] = v;
-          }
-        } else {
-          for (int q = threadIdx.x; q < nwb * N * d.NN * DZ; q += blockDim.x) {
-            const int wl = q / (N * d.NN * DZ), rem = q % (N * d.NN * DZ);
-            const int i = rem / (d.NN * DZ), I = (rem / DZ) % d.NN, z = rem % DZ;
-            const int p = d.n_ee + i * d.NN + I;
-            ctw[(((w0 + wl) * L + n) * d.n_pairs + p) * DZ + z] = CZ[(wl * N + i) * LDZ + z] * P[pl.Y + I * DZ + z];
-          }
-          {
-            // d/d Y_I = sum over layers and electrons of w_iI d/d z_i (this layer's share)
-            for (int q = threadIdx.x; q < d.NN * DZ; q += blockDim.x) {
-              const int I = q / DZ, z = q % DZ;
-              TN s = 0;
-              for (int row = 0; row < R; ++row) {
-                const int wl = row / N, i = row % N;
-                const TN* fv = filt + (w0 + wl) * fl_stride * L + n * fl_stride;
-                s += fv[(int64_t)(d.n_ee + i * d.NN + I) * DZ + z] * CZ[row * LDZ + z];
-              }
-              const bool wr = first && n == L - 1;
-              slot[pl.Y + q] = wr ? s : slot[pl.Y + q] + s;
-            }
-          }
-        }
-        __syncthreads();
-      }
       // h = x W_h + b_h
-      outer_mfma<TN, false>(X, LDX, DX, CH, LDZ, DZ, R, slot + Lp.hW, first);
-      colsum_acc<TN>(CH, LDZ, DZ, R, slot + Lp.hb, first);
+      {
+        TN* oc = op.ch + ((int64_t)n * nw * N + row0) * DZ;
+        for (int q = threadIdx.x; q < R * DZ; q += blockDim.x) oc[q] = CH[(q >> sz) * LDZ + (q & (DZ - 1))];
+      }
+      colsum<TN>(CH, LDZ, DZ, R, sml + sm.hb);
       gemm_mfma_wt<TN>(CH, LDZ, R, DZ, P + Lp.hW, DX, CX, LDX, true);
       __syncthreads();
     }
     // x^(0) = x0 for every electron
-    colsum_acc<TN>(CX, LDX, DX, R, slot + pl.x0, first);
+    colsum<TN>(CX, LDX, DX, R, small + sm.x0);
+  }
+}
+
+// The parameters that are no weight matrix of k_wgrad, per (slot, parameter):
+// the last backflow layer W3 [DX][M] (M is no tile width: a thread per entry,
+// the rows of a group in order), then the groups' sums.
+template <typename TN>
+__global__ __launch_bounds__(kThreads) void k_wgrad_small(Dims d, ParamLayout pl, UnitsOfWalkers units,
+                                                          const TN* __restrict__ a2, const TN* __restrict__ cf,
+                                                          const TN* __restrict__ small, TN* __restrict__ slots,
+                                                          int64_t slot_len) {
+  const SmallSums sm(d);
+  const int64_t s = blockIdx.y;
+  const int q = blockIdx.x * blockDim.x + threadIdx.x, n3 = d.DX * d.M;
+  TN* out = slots + s * slot_len;
+  const int64_t nu = units.count(s);
+  if (q < n3) {
+    const int a = q / d.M, b = q - a * d.M;
+    TN acc = 0;
+    for (int64_t u = 0; u < nu; ++u) {
+      int64_t x0, y0;
+      int n;
+      units.rows(s, u, d.N, x0, y0, n);
+      const TN* x = a2 + x0 * d.DX + a;
+      const TN* y = cf + y0 * d.M + b;
+      TN v = 0;
+      for (int r0 = 0; r0 < n; r0 += 8) {
+        TN xv[8], yv[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const int r = min(r0 + k, n - 1);
+          xv[k] = x[r * d.DX];
+          yv[k] = y[r * d.M];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          if (r0 + k < n) v += xv[k] * yv[k];
+      }
+      acc = u == 0 ? v : acc + v;
+    }
+    out[pl.kW3 + q] = acc;
+    return;
+  }
+  const int e = q - n3;
+  if (e >= sm.total) return;
+  auto sum = [&](int at) {
+    TN acc = 0;
+    for (int64_t u = 0; u < nu; ++u) {
+      const TN v = small[(s + u * units.slots) * sm.total + at];
+      acc = u == 0 ? v : acc + v;
+    }
+    return acc;
+  };
+  if (e < sm.layer) {
+    const int at[8] = {sm.eW3, sm.eb3, sm.eb2, sm.eb1, sm.kb3, sm.kb2, sm.kb1, sm.x0};
+    const int64_t to[8] = {pl.eW3, pl.eb3, pl.eb2, pl.eb1, pl.kb3, pl.kb2, pl.kb1, pl.x0};
+#pragma unroll
+    for (int k = 7; k >= 0; --k)
+      if (e >= at[k]) {
+        out[to[k] + e - at[k]] = sum(e);
+        break;
+      }
+    return;
+  }
+  const int n = (e - sm.layer) / sm.step, o = (e - sm.layer) % sm.step;
+  if (o < sm.hb) {
+    const TN v = sum(e);
+    for (int ch = 0; ch < 3; ++ch) out[pl.layer[n].gb[ch] + o] = v;
+  } else if (o < sm.Y) {
+    out[pl.layer[n].hb + o - sm.hb] = sum(e);
+  } else if (n == 0) {  // one embedding for all layers: summed layer by layer, last to first
+    TN acc = 0;
+    for (int64_t u = 0; u < nu; ++u)
+      for (int l = d.L - 1; l >= 0; --l) {
+        const TN v = small[(s + u * units.slots) * sm.total + sm.layer + l * sm.step + o];
+        acc = u == 0 && l == d.L - 1 ? v : acc + v;
+      }
+    out[pl.Y + o - sm.Y] = acc;
   }
 }
 
@@ -559,28 +733,39 @@ static size_t bwd_net_union(const Dims& d, int WB) {
   const int LDX = ld_pad<TN>(d.DX), LDZ = ld_pad<TN>(d.DZ), LDM = ld_pad<TN>((d.M + 15) & ~15);
   const size_t RW = (size_t)WB * d.N;
   const size_t heads = 3 * RW * LDX + RW * LDM + 6 * (size_t)WB * LDX;  // kappa buffers, then the eta ones
-  const size_t layers = 4 * RW * LDZ;
+  const size_t layers = 5 * RW * LDZ;
   return std::max(heads, layers);
 }
 
 // LDS of k_bwd_net; with `arena` the union region lives in global memory
 template <typename TN>
 static size_t bwd_net_lds(const Dims& d, int WB, bool arena = false) {
-  const int LDX = ld_pad<TN>(d.DX);
   const size_t RW = (size_t)WB * d.N;
-  return (size_t)((d.N * d.N + 3) & ~3) * sizeof(int) +
-         ((size_t)((WB + 3) & ~3) + 2 * RW * LDX + (arena ? 0 : bwd_net_union<TN>(d, WB))) * sizeof(TN);
+  return (size_t)((d.N * d.N + 3) & ~3) * sizeof(int) + (size_t)((d.n_ee + 7) & ~7) * 2 +
+         (size_t)((2 * d.P * d.M + 15) & ~15) +
+         ((size_t)((WB + 3) & ~3) + RW * ld_pad<TN>(d.DX) + (arena ? 0 : bwd_net_union<TN>(d, WB))) * sizeof(TN);
 }
 
+// Walkers per group: the unit of every sum over rows in the gradient (and so
+// part of its FP32 rounding).  About 64 rows, as far as a block that also
+// holds the layer inputs stays within half a CU's LDS.
 template <typename TN>
 static int bwd_wb(const Dims& d) {
+  auto bytes = [&](int wb) {
+    const size_t LDX = ld_pad<TN>(d.DX), LDZ = ld_pad<TN>(d.DZ), LDM = ld_pad<TN>((d.M + 15) & ~15);
+    const size_t RW = (size_t)wb * d.N;
+    return (size_t)((d.N * d.N + 3) & ~3) * sizeof(int) +
+           ((size_t)((wb + 3) & ~3) + 2 * RW * LDX +
+            std::max(3 * RW * LDX + RW * LDM + 6 * (size_t)wb * LDX, 4 * RW * LDZ)) *
+               sizeof(TN);
+  };
   int wb = std::max(1, 64 / d.N);
-  while (wb > 1 && bwd_net_lds<TN>(d, wb) > 80 * 1024) --wb;
+  while (wb > 1 && bytes(wb) > 80 * 1024) --wb;
   return wb;
 }
 
 // k_bwd_net keeps its union region in a global arena when the whole block
-// does not fit in LDS (the 30-electron system in FP64)
+// does not fit in LDS (64 electrons of width 128 in FP64)
 template <typename TN>
 static bool bwd_net_arena(const Dims& d) {
   return bwd_net_lds<TN>(d, bwd_wb<TN>(d)) > 160 * 1024;
@@ -599,6 +784,12 @@ static int bwd_filter_rows(const Dims& d, bool fp32, bool full) {
 
 static size_t filt_fsz(const Dims& d) { return (size_t)d.K * d.DZ + d.DZ + (size_t)d.DZ * d.DZ + d.DZ; }
 
+// elements of the row tables that k_bwd_net leaves for the weight gradients
+static size_t net_ops_elems(const Dims& d, int64_t nw) {
+  const size_t rows = (size_t)nw * d.N;
+  return (size_t)d.L * rows * (4 * (size_t)d.DZ + d.DX) + rows * (4 * (size_t)d.DX + d.M) + 4 * (size_t)nw * d.DX;
+}
+
 size_t backward_scratch_bytes(const pn_ctx* c, int64_t tile, bool fp32) {
   const Dims& d = c->d;
   const size_t tn = fp32 ? sizeof(float) : sizeof(double);
@@ -607,10 +798,10 @@ size_t backward_scratch_bytes(const pn_ctx* c, int64_t tile, bool fp32) {
   b += (size_t)kSlotsFilter * d.L * 3 * filt_fsz(d) * tn;          // filter slots
   b += (size_t)tile * d.L * d.n_pairs * d.DZ * tn;                 // filter cotangents
   const bool arena = fp32 ? bwd_net_arena<float>(d) : bwd_net_arena<double>(d);
-  if (arena)
-    b += (size_t)kSlotsNet * (fp32 ? bwd_net_union<float>(d, bwd_wb<float>(d)) : bwd_net_union<double>(d, bwd_wb<double>(d))) *
-         tn;
-  return b + 1024;
+  const int wb = fp32 ? bwd_wb<float>(d) : bwd_wb<double>(d);
+  if (arena) b += (size_t)kSlotsNet * (fp32 ? bwd_net_union<float>(d, wb) : bwd_net_union<double>(d, wb)) * tn;
+  b += (net_ops_elems(d, tile) + (size_t)((tile + wb - 1) / wb) * SmallSums(d).total) * tn;
+  return b + 32 * 256;
 }
 
 bool backward_supported(const pn_ctx* c, bool fp32) {
@@ -630,23 +821,70 @@ static void run_backward(const pn_ctx* c, hipStream_t s, int64_t nw, const doubl
   TN* fslot = gslot + (size_t)kSlotsNet * np;
   TN* ctw = fslot + (size_t)kSlotsFilter * d.L * 3 * filt_fsz(d);
   const int WB = bwd_wb<TN>(d);
-  const bool use_arena = bwd_net_arena<TN>(d);
-  TN* arena = use_arena ? ctw + (size_t)L.tile * d.L * d.n_pairs * d.DZ : nullptr;
-  const int64_t arena_elems = use_arena ? (int64_t)bwd_net_union<TN>(d, WB) : 0;
-  const size_t lds = bwd_net_lds<TN>(d, WB, use_arena);
-  if (lds > 65536)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bwd_net<TN>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)lds);
   const int64_t ng = (nw + WB - 1) / WB;
+  const int64_t rows = nw * d.N;
+  const SmallSums sm(d);
+  // what follows the filter cotangents, in 256-byte steps
+  TN* at = ctw + (size_t)L.tile * d.L * d.n_pairs * d.DZ;
+  auto take = [&](size_t elems) {
+    at = reinterpret_cast<TN*>((reinterpret_cast<uintptr_t>(at) + 255) & ~(uintptr_t)255);
+    TN* p = at;
+    at += elems;
+    return p;
+  };
+  const bool use_arena = bwd_net_arena<TN>(d);
+  const int64_t arena_elems = use_arena ? (int64_t)bwd_net_union<TN>(d, WB) : 0;
+  TN* arena = use_arena ? take((size_t)kSlotsNet * arena_elems) : nullptr;
+  NetOps<TN> op;
+  op.z = take((size_t)d.L * 3 * rows * d.DZ);
+  op.cx = take((size_t)d.L * rows * d.DX);
+  op.ch = take((size_t)d.L * rows * d.DZ);
+  op.a1 = take((size_t)rows * d.DX);
+  op.c2 = take((size_t)rows * d.DX);
+  op.c1 = take((size_t)rows * d.DX);
+  op.a2 = take((size_t)rows * d.DX);
+  op.cf = take((size_t)rows * d.M);
+  op.s = take((size_t)nw * d.DX);
+  op.e1 = take((size_t)nw * d.DX);
+  op.ec1 = take((size_t)nw * d.DX);
+  op.ec2 = take((size_t)nw * d.DX);
+  op.small = take((size_t)ng * sm.total);
+  const TN* xval = reinterpret_cast<const TN*>(ws + L.xval);
+  const size_t lds = bwd_net_lds<TN>(d, WB, use_arena);
+  // a block that takes more than half the CU's LDS runs alone on it
+  const int nt = lds > 80 * 1024 ? 512 : 256;
+  auto net_kernel = nt == 512 ? &k_bwd_net<TN, 512> : &k_bwd_net<TN, 256>;
+  if (lds > 65536)
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(net_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)lds);
   const int nb_net = (int)std::min<int64_t>(ng, kSlotsNet);
-  hipLaunchKernelGGL(k_bwd_net<TN>, dim3(nb_net), dim3(kThreads), lds, s, d, c->t, nw, WB, P, c->pl,
-                     reinterpret_cast<const TN*>(ws + L.xval), reinterpret_cast<const TN*>(ws + L.hval),
-                     reinterpret_cast<const TN*>(ws + L.filt), reinterpret_cast<const double*>(ws + L.phi),
-                     reinterpret_cast<const double*>(ws + L.ginv), reinterpret_cast<const double*>(ws + L.wdet), ct,
-                     ctw, gslot, np, full ? reinterpret_cast<const double*>(ws + L.ctfpart) : nullptr, L.n_chunks,
+  hipLaunchKernelGGL(net_kernel, dim3((unsigned)(use_arena ? nb_net : ng)), dim3(nt), lds, s, d, c->t, nw, WB, P, c->pl,
+                     xval, reinterpret_cast<const TN*>(ws + L.hval), reinterpret_cast<const TN*>(ws + L.filt),
+                     reinterpret_cast<const double*>(ws + L.phi), reinterpret_cast<const double*>(ws + L.ginv),
+                     reinterpret_cast<const double*>(ws + L.wdet), ct, ctw,
+                     full ? reinterpret_cast<const double*>(ws + L.ctfpart) : nullptr, L.n_chunks,
                      full ? reinterpret_cast<const TN*>(ws + L.cthv) : nullptr,
                      full ? reinterpret_cast<const TN*>(ws + L.ctkc) : nullptr,
-                     full ? reinterpret_cast<const TN*>(ws + L.ctec) : nullptr, arena, arena_elems);
+                     full ? reinterpret_cast<const TN*>(ws + L.ctec) : nullptr, op, arena, arena_elems);
+  const UnitsOfWalkers units{nw, WB, kSlotsNet};
+  WMats<TN> mats;
+  mats.n = 0;
+  auto mat = [&](const TN* X, const TN* Y, int64_t out, int A, int B, int rpw) {
+    mats.m[mats.n++] = WMat<TN>{X, Y, out, A, B, rpw, 0};
+  };
+  for (int n = 0; n < d.L; ++n) {
+    for (int ch = 0; ch < 3; ++ch)
+      mat(op.z + (size_t)(n * 3 + ch) * rows * d.DZ, op.cx + (size_t)n * rows * d.DX, c->pl.layer[n].gW[ch], d.DZ, d.DX,
+          d.N);
+    mat(xval + (size_t)n * rows * d.DX, op.ch + (size_t)n * rows * d.DZ, c->pl.layer[n].hW, d.DX, d.DZ, d.N);
+  }
+  mat(op.a1, op.c2, c->pl.kW2, d.DX, d.DX, d.N);
+  mat(xval + (size_t)d.L * rows * d.DX, op.c1, c->pl.kW1, d.DX, d.DX, d.N);
+  mat(op.e1, op.ec2, c->pl.eW2, d.DX, d.DX, 1);
+  mat(op.s, op.ec1, c->pl.eW1, d.DX, d.DX, 1);
+  launch_wgrad<TN>(s, mats, units, nb_net, gslot, np, false);
+  hipLaunchKernelGGL(k_wgrad_small<TN>, dim3((unsigned)((d.DX * d.M + sm.total + kThreads - 1) / kThreads), nb_net),
+                     dim3(kThreads), 0, s, d, c->pl, units, op.a2, op.cf, op.small, gslot, np);
   const int n_same = d.n_up * (d.n_up - 1) / 2 + d.n_dn * (d.n_dn - 1) / 2;
   const int64_t max_np = std::max<int64_t>(std::max(n_same, d.n_ee - n_same), (int64_t)d.N * d.NN);
   const int PT = bwd_filter_rows(d, sizeof(TN) == sizeof(float), full);

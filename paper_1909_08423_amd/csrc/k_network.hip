@@ -135,8 +135,8 @@ __global__ __launch_bounds__(kThreads, sizeof(TN) == 4 ? 3 : 2) void k_net_value
   __syncthreads();
   auto save_x = [&](int n) {  // x^(n), for the adjoints
     for (int q = threadIdx.x; q < R * DX; q += blockDim.x) {
-      const int row = q >> sx, x = q & (DX - 1), wl = rN.div(row);
-      xval[(((w0 + wl) * (d.L + 1) + n) * N + (row - wl * N)) * DX + x] = X[row * LDX + x];
+      const int row = q >> sx, x = q & (DX - 1);
+      xval[((n * nw + w0) * N) * DX + q] = X[row * LDX + x];
     }
   };
   for (int n = 0; n < d.L; ++n) {

@@ -117,7 +117,7 @@ struct WsLayout {
   size_t ftan;         // [tile][n_chunks][N][T+1][M] double
   size_t jtan;         // [tile][n_chunks][T+1] double
   size_t partial;      // [tile][n_chunks][2]
-  size_t xval;         // [tile][L+1][N][DX] activations (backward only)
+  size_t xval;         // [L+1][walkers of the launch][N][DX] activations (backward only)
   size_t adj;          // backward scratch
   size_t gpart;        // [n_blocks][n_params] per-block parameter gradients
   // full adjoint (cotangents on grad / lap / E_loc)
