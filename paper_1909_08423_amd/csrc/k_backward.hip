@@ -439,11 +439,10 @@ __global__ __launch_bounds__(kThreads) void k_wgrad_small(Dims d, ParamLayout pl
     const int a = q / d.M, b = q - a * d.M;
     TN acc = 0;
     for (int64_t u = 0; u < nu; ++u) {
-      int64_t x0, y0;
-      int n;
-      units.rows(s, u, d.N, x0, y0, n);
-      const TN* x = a2 + x0 * d.DX + a;
-      const TN* y = cf + y0 * d.M + b;
+      int64_t w0;
+      const int n = units.group(s, u, w0) * d.N;
+      const TN* x = a2 + w0 * d.N * d.DX + a;
+      const TN* y = cf + w0 * d.N * d.M + b;
       TN v = 0;
       for (int r0 = 0; r0 < n; r0 += 8) {
         TN xv[8], yv[8];
@@ -721,7 +720,23 @@ __global__ __launch_bounds__(kThreads) void k_bwd_reduce(Dims d, ParamLayout pl,
   }
   double s = 0.0;
   for (int b = 0; b < n_net; ++b) s += (double)gslot[(size_t)b * n_params + q];
-  for (int b = 0; b < n_tan; ++b) s += (double)tslot[(size_t)b * n_params + q];
+  // the tangent adjoint's slots hold what depends on the tangents: the
+  // products without a bias, from layer 1 on for h, and the nuclear embeddings
+  bool tan = (q >= pl.Y && q < pl.Y + d.NN * d.DZ);
+  for (int n = 0; n < d.L; ++n) {
+    const ParamLayout::Layer& Lp = pl.layer[n];
+    const int64_t xz = (int64_t)d.DX * d.DZ;
+    tan = tan || (n > 0 && q >= Lp.hW && q < Lp.hW + xz);
+    for (int ch = 0; ch < 3; ++ch) tan = tan || (q >= Lp.gW[ch] && q < Lp.gW[ch] + xz);
+  }
+  const int64_t xx = (int64_t)d.DX * d.DX;
+  if (!(d.flags & PN_NET_NO_JASTROW))
+    tan = tan || (q >= pl.eW1 && q < pl.eW1 + xx) || (q >= pl.eW2 && q < pl.eW2 + xx) ||
+          (q >= pl.eW3 && q < pl.eW3 + d.DX);
+  if (!(d.flags & PN_NET_NO_BACKFLOW))
+    tan = tan || (q >= pl.kW1 && q < pl.kW1 + xx) || (q >= pl.kW2 && q < pl.kW2 + xx) ||
+          (q >= pl.kW3 && q < pl.kW3 + (int64_t)d.DX * d.M);
+  for (int b = 0; tan && b < n_tan; ++b) s += (double)tslot[(size_t)b * n_params + q];
   grad[q] += s;
 }
 
@@ -870,7 +885,7 @@ static void run_backward(const pn_ctx* c, hipStream_t s, int64_t nw, const doubl
   WMats<TN> mats;
   mats.n = 0;
   auto mat = [&](const TN* X, const TN* Y, int64_t out, int A, int B, int rpw) {
-    mats.m[mats.n++] = WMat<TN>{X, Y, out, A, B, rpw, 0};
+    mats.m[mats.n++] = WMat<TN>{X, Y, out, 0, 0, A, B, rpw, 0};
   };
   for (int n = 0; n < d.L; ++n) {
     for (int ch = 0; ch < 3; ++ch)
@@ -882,7 +897,7 @@ static void run_backward(const pn_ctx* c, hipStream_t s, int64_t nw, const doubl
   mat(xval + (size_t)d.L * rows * d.DX, op.c1, c->pl.kW1, d.DX, d.DX, d.N);
   mat(op.e1, op.ec2, c->pl.eW2, d.DX, d.DX, 1);
   mat(op.s, op.ec1, c->pl.eW1, d.DX, d.DX, 1);
-  launch_wgrad<TN>(s, mats, units, nb_net, gslot, np, false);
+  launch_wgrad<TN>(s, mats, units, nb_net, gslot, np);
   hipLaunchKernelGGL(k_wgrad_small<TN>, dim3((unsigned)((d.DX * d.M + sm.total + kThreads - 1) / kThreads), nb_net),
                      dim3(kThreads), 0, s, d, c->pl, units, op.a2, op.cf, op.small, gslot, np);
   const int n_same = d.n_up * (d.n_up - 1) / 2 + d.n_dn * (d.n_dn - 1) / 2;

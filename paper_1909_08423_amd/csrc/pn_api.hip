@@ -26,7 +26,7 @@ void launch_backward(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r
 size_t backward_filter_lds_bytes(const Dims& d, bool fp32, bool full);
 size_t adj_slater_lds_bytes(const Dims& d, int T);
 template <typename TN>
-size_t tangent_adj_arena_elems(const Dims& d, int T);
+size_t tangent_adj_ops_bytes(const Dims& d, int T, int64_t nw);
 template <typename TN>
 size_t tangent_adj_lds_bytes(const Dims& d, int T, bool global_arena);
 size_t backward_scratch_bytes(const pn_ctx* c, int64_t tile, bool fp32);
@@ -131,9 +131,9 @@ bool solve3(double M[3][3], double b[3], double x[3]) {
 // The tangent pass's buffers exist in modes 0 and 2 only.
 enum { kPlanForward = 0, kPlanValueAdjoint = 1, kPlanFullAdjoint = 2, kPlanValueOnly = 3 };
 
-// chunk size of the full adjoint: the largest T in 1..6 whose tangent-adjoint
-// block keeps its row buffers in LDS; when none fits, the row buffers go to a
-// per-block global arena and T is the largest whose small tables fit.  The
+// chunk size of the full adjoint: the largest T in 1..6 with five row tables of
+// a chunk within the LDS; when none fits, the largest whose pair tables fit.
+// The adjoint itself needs less; the chunks are part of the FP32 rounding.  The
 // forward tangent pass runs with the same chunks, so its block must fit too.
 void plan_full_adjoint(const Dims& d, bool fp64, WsLayout& L) {
   auto lds = [&](int T, bool ga) {
@@ -149,15 +149,16 @@ void plan_full_adjoint(const Dims& d, bool fp64, WsLayout& L) {
       if (!tangent_chunk_supported(T)) continue;
       if (lds(T, ga) <= kLdsMax && adj_slater_lds_bytes(d, T) <= kLdsMax) {
         L.T = T;
-        L.tadj_global = ga;
+        L.lds_tadj = lds(T, ga);
         break;
       }
     }
   }
-  if (L.T == 0) L.T = 1;  // reported unsupported by the caller (LDS over the limit)
-  L.lds_tadj = lds(L.T, L.tadj_global);
+  if (L.T == 0) {  // reported unsupported by the caller (LDS over the limit)
+    L.T = 1;
+    L.lds_tadj = lds(1, true);
+  }
   L.lds_adjdet = adj_slater_lds_bytes(d, L.T);
-  L.tadj_arena = fp64 ? tangent_adj_arena_elems<double>(d, L.T) : tangent_adj_arena_elems<float>(d, L.T);
 }
 
 // `budget`: workspace bytes the walker tile is sized for; min_tile: the
@@ -346,8 +347,8 @@ WsLayout plan(const pn_ctx* c, int64_t nw, pn_precision prec, int mode, size_t b
     L.ctkc = region((size_t)tile * 4 * N * d.DX * tn);
     L.ctec = region((size_t)tile * 4 * d.DX * tn);
     L.ct0 = region((size_t)tile * 8);
-    L.tslot = region(((size_t)kSlotsTanAdj * c->pl.total + (L.tadj_global ? (size_t)kSlotsTanAdj * L.tadj_arena : 0)) *
-                     tn);
+    L.tslot = region((size_t)kSlotsTanAdj * c->pl.total * tn);
+    L.tanops = region(fp64 ? tangent_adj_ops_bytes<double>(d, L.T, tile) : tangent_adj_ops_bytes<float>(d, L.T, tile));
   }
   L.total = off;
   return L;

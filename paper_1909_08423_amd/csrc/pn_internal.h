@@ -122,10 +122,8 @@ struct WsLayout {
   size_t gpart;        // [n_blocks][n_params] per-block parameter gradients
   // full adjoint (cotangents on grad / lap / E_loc)
   bool full;
-  bool tadj_global;    // tangent-adjoint row buffers in a global arena (else LDS)
-  size_t lds_tadj;     // dynamic LDS of the tangent adjoint
+  size_t lds_tadj;     // bytes of the full adjoint's chunk rule
   size_t lds_adjdet;   // dynamic LDS of the determinant adjoint
-  size_t tadj_arena;   // elements of one block's row buffers
   size_t xsave;        // [tile][n_chunks][L][N(T+1)][DX] net type: layer inputs of the tangent pass
   size_t detres;       // [tile][n_chunks][P][2][T+1] per-determinant derivatives
   size_t gradf;        // [tile][3N] gradient of ln|psi|
@@ -140,7 +138,8 @@ struct WsLayout {
   size_t ctkc;         // [tile][2][2][N][DX]    net type
   size_t ctec;         // [tile][2][2][DX]       net type
   size_t ct0;          // [tile] zeros (absent ln|psi| cotangent)
-  size_t tslot;        // [kSlotsTanAdj][n_params] + global arena, net type
+  size_t tslot;        // [kSlotsTanAdj][n_params] net type
+  size_t tanops;       // tables of one batch of walkers of the tangent adjoint
   // low-rank determinant path (forward only)
   bool lowrank;
   size_t lds_lr;       // dynamic LDS of the low-rank tangent kernel
@@ -153,7 +152,7 @@ struct WsLayout {
   size_t total;
 };
 
-constexpr int kSlotsTanAdj = 512;  // blocks (and gradient slots) of the tangent adjoint
+constexpr int kSlotsTanAdj = 512;  // gradient slots of the tangent adjoint
 
 constexpr int kGeoStride(int N) { return 4 + 6 * N; }  // V, gamma, lap_gamma, pad, N*(grad3, hess3)
 

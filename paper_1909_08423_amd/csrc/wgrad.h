@@ -30,8 +30,9 @@ struct WMat {
   const TN* X;   // [rows][A]
   const TN* Y;   // [rows][B]
   int64_t out;   // offset of the [A][B] result in a slot
+  int64_t xu, yu;  // elements from one unit to the next (chunks; the walkers' tables are contiguous)
   int A, B;
-  int rpw;       // UnitsOfWalkers: rows per walker; UnitsOfChunks: 0 = all rows, 1 = the chunk electrons' rows
+  int rows;      // rows per walker, or per chunk (0: those of the chunk's electrons)
   int strip0;    // first strip of this matrix among its launch
 };
 
@@ -45,14 +46,22 @@ struct WMats {
 struct UnitsOfWalkers {
   int64_t nw;
   int wb, slots;
+  __device__ int64_t slot(int64_t s) const { return s; }
+  __device__ bool keep(int64_t) const { return false; }  // one launch makes a slot
   __device__ int64_t count(int64_t s) const {
     const int64_t ng = (nw + wb - 1) / wb;
     return s < ng ? (ng - s + slots - 1) / slots : 0;
   }
-  __device__ void rows(int64_t s, int64_t k, int rpw, int64_t& x0, int64_t& y0, int& n) const {
-    const int64_t w0 = (s + k * slots) * wb;
-    x0 = y0 = w0 * rpw;
-    n = (int)min((int64_t)wb, nw - w0) * rpw;
+  __device__ int group(int64_t s, int64_t k, int64_t& w0) const {  // first walker and their number
+    w0 = (s + k * slots) * wb;
+    return (int)min((int64_t)wb, nw - w0);
+  }
+  template <typename M>
+  __device__ void rows(int64_t s, int64_t k, const M& m, int64_t& x0, int64_t& y0, int& n) const {
+    int64_t w0;
+    n = group(s, k, w0) * m.rows;
+    x0 = w0 * m.rows * m.A;
+    y0 = w0 * m.rows * m.B;
   }
 };
 
@@ -75,10 +84,11 @@ __device__ __forceinline__ void load_rows(const TN* p, int ld, int r0, int n, TN
   }
 }
 
-// keep: the slots already hold the sums of earlier units (else they are set).
+// UNITS: slot() is the slot of local index s, keep() whether it already holds
+// the sum of earlier units (else it is set), rows() where a unit's rows are.
 template <typename TN, typename UNITS, int NA, int NB>
 __global__ __launch_bounds__(256) void k_wgrad(WMats<TN> mats, UNITS units, int n_slots, int n_strips, int bps,
-                                               TN* __restrict__ slots, int64_t slot_len, bool keep) {
+                                               TN* __restrict__ slots, int64_t slot_len) {
   typedef typename MfmaTile<TN>::acc_t acc_t;
   const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
   // blocks b, b + 8, ... run on one XCD: a slot's bps blocks stay together
@@ -92,7 +102,8 @@ __global__ __launch_bounds__(256) void k_wgrad(WMats<TN> mats, UNITS units, int 
   const int a0 = local / nbs * (16 * NA), b0 = local % nbs * (16 * NB);
   const TN* X = m.X + a0 + NA * c16;
   const TN* Y = m.Y + b0 + NB * c16;
-  TN* out = slots + s * slot_len + m.out;
+  TN* out = slots + units.slot(s) * slot_len + m.out;
+  const bool keep = units.keep(s);
   acc_t acc[NA][NB];
   const int64_t nu = units.count(s);
 #pragma unroll
@@ -105,9 +116,9 @@ __global__ __launch_bounds__(256) void k_wgrad(WMats<TN> mats, UNITS units, int 
   for (int64_t u = 0; u < nu; ++u) {
     int64_t x0, y0;
     int n;
-    units.rows(s, u, m.rpw, x0, y0, n);
-    const TN* xu = X + x0 * m.A;
-    const TN* yu = Y + y0 * m.B;
+    units.rows(s, u, m, x0, y0, n);
+    const TN* xu = X + x0;
+    const TN* yu = Y + y0;
     acc_t c[NA][NB];
 #pragma unroll
     for (int a = 0; a < NA; ++a)
@@ -144,8 +155,8 @@ __global__ __launch_bounds__(256) void k_wgrad(WMats<TN> mats, UNITS units, int 
 // All matrices of `all`, one launch per strip shape.  FP32 strips are two
 // tiles high where A allows it; FP64 accumulators take twice the registers.
 template <typename TN, typename UNITS>
-void launch_wgrad(hipStream_t s, const WMats<TN>& all, const UNITS& units, int n_slots, TN* slots, int64_t slot_len,
-                  bool keep) {
+void launch_wgrad(hipStream_t s, const WMats<TN>& all, const UNITS& units, int n_slots, TN* slots,
+                  int64_t slot_len) {
   auto launch = [&](auto na, auto nb) {
     constexpr int NA = decltype(na)::value, NB = decltype(nb)::value;
     WMats<TN> ms;
@@ -164,7 +175,7 @@ void launch_wgrad(hipStream_t s, const WMats<TN>& all, const UNITS& units, int n
     const int bps = (strips + 3) / 4;
     const unsigned grid = (unsigned)((n_slots + 7) / 8 * 8 * bps);
     hipLaunchKernelGGL((k_wgrad<TN, UNITS, NA, NB>), dim3(grid), dim3(256), 0, s, ms, units, n_slots, strips, bps,
-                       slots, slot_len, keep);
+                       slots, slot_len);
   };
   using one = std::integral_constant<int, 1>;
   using two = std::integral_constant<int, 2>;
