@@ -35,7 +35,7 @@ namespace {
 
 constexpr int kSlotsNet = 512;     // gradient slots of the network weights
 constexpr int kSlotsFilter = 256;  // blocks per (layer, channel) of k_bwd_filter
-constexpr int kFiltRows = 32;      // (walker, pair) rows per tile of k_bwd_filter
+constexpr int kFiltRows = 32;      // (walker, pair) rows per tile of k_bwd_filter, at most
 
 // What k_bwd_net leaves behind for the weight gradients ([walker][row]
 // tables, contiguous over the walkers of a launch) and, per group of walkers,
@@ -509,74 +509,120 @@ __global__ __launch_bounds__(kThreads) void k_wgrad_small(Dims d, ParamLayout pl
 //   ct u  = ct a0 s + ct a1 s' ud + ct a2 (s' u2 + s'' (d ud)^2)
 //   ct ud = ct a1 s + 2 ct a2 s' d (d ud),   ct u2 = ct a2 s
 //   dW1 += e^T ct u + (e'/d)^T ct ud + e''^T ct u2,  db1 += ct u.
-template <typename TN, bool JETS, int PT>
-__global__ __launch_bounds__(kThreads) void k_bwd_filter(Dims d, DevTables t, int64_t nw, const double* __restrict__ r,
-                                                         const TN* __restrict__ P, ParamLayout pl,
-                                                         const TN* __restrict__ ctw, const TN* __restrict__ ctww,
-                                                         const TN* __restrict__ ctwd, const TN* __restrict__ ctw2,
-                                                         TN* __restrict__ fslot, int n_same) {
+// A block walks row tiles of PT (walker, pair) rows with its weight slabs in
+// registers.  Per tile: features and filter cotangents to LDS, then (one wave
+// per 16 x 16 tile of the hidden layer) both products and the activation's
+// reverse in the accumulators, then the weight gradients.  The next tile's
+// distances are computed, and its cotangents requested, one tile ahead.  Bound
+// by the latency of those steps (two blocks per CU), not by a unit.
+// Measured per launch: 5.8 -> 2.8 ms at 2048 walkers of the 30-electron
+// diatomic and 0.57 -> 0.22 ms at 4096 walkers of a ten-electron atom (FP32),
+// 1.27 -> 0.57 ms with jets at 1024 walkers of a ten-atom chain (FP64).
+template <typename TN, bool JETS, int PT, int KQ1, int KQ2>
+__global__ __launch_bounds__(KQ2 == 16 ? 512 : 256, JETS || sizeof(TN) == 8 ? 2 : 4) void k_bwd_filter(
+    Dims d, DevTables t, int64_t nw, const double* __restrict__ r, const TN* __restrict__ P, ParamLayout pl,
+    const TN* __restrict__ ctw, const TN* __restrict__ ctww, const TN* __restrict__ ctwd, const TN* __restrict__ ctw2,
+    TN* __restrict__ fslot, int n_same) {
   extern __shared__ __align__(16) char smem[];
-  constexpr int NJ = JETS ? 3 : 1;
-  const int layer = blockIdx.y / 3, ch = blockIdx.y % 3;
-  const int K = d.K, DZ = d.DZ, L = d.L;
-  const int LDK = ld_pad<TN>(K), LDZ = ld_pad<TN>(DZ);
+  typedef typename MfmaTile<TN>::acc_t acc_t;
+  constexpr int NJ = JETS ? 3 : 1, K = 4 * KQ1, DZ = 4 * KQ2, NT = KQ2 == 16 ? 512 : 256, NW = NT / 64;
+  constexpr int LDK = ld_pad<TN>(K), LDZ = ld_pad<TN>(DZ);
   constexpr int RPG = PT / 4;  // rows of a tile per lane group of the MFMA reduction
+  constexpr int nz = DZ / 16, nt1 = (K / 16) * nz, nt = nt1 + nz * nz, kTiles = (nt + NW - 1) / NW;
+  constexpr int nh = nz * (PT / 16), kHid = (nh + NW - 1) / NW;  // hidden-layer tiles, per wave
+  constexpr int kCw = PT * DZ / NT;                              // cotangent entries per thread and jet
+  const int layer = blockIdx.y / 3, ch = blockIdx.y % 3, L = d.L;
   const int p_lo = ch == 0 ? 0 : (ch == 1 ? n_same : d.n_ee);
   const int p_hi = ch == 0 ? n_same : (ch == 1 ? d.n_ee : d.n_pairs);
   const int np = p_hi - p_lo;
   const int64_t nrows = nw * np;
-  double* dd = reinterpret_cast<double*>(smem);  // [PT]
-  TN* E = reinterpret_cast<TN*>(dd + PT);        // [NJ][PT][LDK] feature jets
-  TN* U = E + NJ * PT * LDK;                     // [NJ][PT][LDZ] hidden jets, then activations
+  double* dd = reinterpret_cast<double*>(smem);                  // [2][PT] distances, this tile's and the next's
+  int64_t* oc = reinterpret_cast<int64_t*>(dd + 2 * PT);         // [2][PT] offset of a row in the pair tables
+  int64_t* oe = oc + 2 * PT;                                     // [2][PT] in the ee table, -1 for e-n pairs
+  TN* E = reinterpret_cast<TN*>(oe + 2 * PT);    // [NJ][PT][LDK] feature jets
+  TN* U = E + NJ * PT * LDK;                     // [NJ][PT][LDZ] activations
   TN* CW = U + NJ * PT * LDZ;                    // [NJ][PT][LDZ] d/d (w, w'/d, w'')
-  TN* CU = CW + NJ * PT * LDZ;                   // [NJ][PT][LDZ] d/d activations, then d/d hidden jets
+  TN* CU = CW + NJ * PT * LDZ;                   // [NJ][PT][LDZ] d/d hidden jets
   const ParamLayout::Layer& Lp = pl.layer[layer];
-  const int fsz = K * DZ + DZ + DZ * DZ + DZ;
-  // weight gradients dW1 = sum_k E_k^T CU_k and dW2 = sum_k U_k^T CW_k on
-  // the matrix cores: every wavefront keeps its 16 x 16 output tiles in
-  // registers across all row tiles; the reduction runs over the PT rows of
-  // a tile (32, or 16 where 32 would exceed the LDS).
-  typedef typename MfmaTile<TN>::acc_t acc_t;
-  constexpr int kMaxT = 8;  // tiles per wavefront: (K/16 + DZ/16) * DZ/16 <= 32
+  constexpr int fsz = K * DZ + DZ + DZ * DZ + DZ;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane >> 4, c16 = lane & 15;
-  const int nz = DZ / 16, nt1 = (K / 16) * nz, nt = nt1 + nz * nz;
-  acc_t accs[kMaxT];
+  acc_t accs[kTiles];
 #pragma unroll
-  for (int k = 0; k < kMaxT; ++k)
+  for (int k = 0; k < kTiles; ++k)
 #pragma unroll
     for (int v = 0; v < 4; ++v) accs[k][v] = 0;
-  TN bacc1 = 0, bacc2 = 0;  // thread z < DZ owns db1[z], db2[z]
-  for (int64_t row0 = (int64_t)blockIdx.x * PT; row0 < nrows; row0 += (int64_t)gridDim.x * PT) {
-    const int rows = (int)min((int64_t)PT, nrows - row0);
-    __syncthreads();
-    for (int q = threadIdx.x; q < PT; q += blockDim.x) {
-      double v = 1.0;
-      if (q < rows) {
-        const int64_t gq = row0 + q, w = gq / np;
-        const int p = p_lo + (int)(gq % np);
-        const double* rw = r + w * d.N * 3;
-        double x, y, z;
-        if (p < d.n_ee) {
-          const int i = t.pair_ij[2 * p], j = t.pair_ij[2 * p + 1];
-          x = rw[3 * i] - rw[3 * j];
-          y = rw[3 * i + 1] - rw[3 * j + 1];
-          z = rw[3 * i + 2] - rw[3 * j + 2];
-        } else {
-          const int q2 = p - d.n_ee, i = q2 / d.NN, I = q2 % d.NN;
-          x = rw[3 * i] - t.nuc_xyz[3 * I];
-          y = rw[3 * i + 1] - t.nuc_xyz[3 * I + 1];
-          z = rw[3 * i + 2] - t.nuc_xyz[3 * I + 2];
-        }
-        v = sqrt(x * x + y * y + z * z);
+  TN bacc = 0;  // thread z < DZ owns db1[z], thread DZ + z db2[z] (different waves where DZ is a wave)
+  // weight slabs of this wave's column of hidden tiles (ct = wv % nz for each of them)
+  const int col = (wv % nz) * 16 + c16;
+  TN w1[KQ1], w2[KQ2];
+#pragma unroll
+  for (int s = 0; s < KQ1; ++s) w1[s] = P[Lp.w1W[ch] + (g * KQ1 + s) * DZ + col];
+#pragma unroll
+  for (int s = 0; s < KQ2; ++s) w2[s] = P[Lp.w2W[ch] + col * DZ + g * KQ2 + s];
+  const TN b1 = P[Lp.w1b[ch] + col];
+  // distance and table offsets of row q of the tile at row0
+  auto locate = [&](int64_t row0, int buf) {
+    const int q = (int)threadIdx.x - (NT - PT);  // the last threads: the first ones sum the biases
+    if (q < 0) return;
+    double v = 1.0;
+    int64_t o = 0, e = -1;
+    if (row0 + q < nrows) {
+      const int gq = (int)(row0 + q), w = gq / np, p = p_lo + gq - w * np;
+      const double* rw = r + (int64_t)w * d.N * 3;
+      double x, y, z;
+      if (p < d.n_ee) {
+        const int i = t.pair_ij[2 * p], j = t.pair_ij[2 * p + 1];
+        x = rw[3 * i] - rw[3 * j];
+        y = rw[3 * i + 1] - rw[3 * j + 1];
+        z = rw[3 * i + 2] - rw[3 * j + 2];
+        e = (((int64_t)w * L + layer) * d.n_ee + p) * DZ;
+      } else {
+        const int q2 = p - d.n_ee, i = q2 / d.NN, I = q2 - i * d.NN;
+        x = rw[3 * i] - t.nuc_xyz[3 * I];
+        y = rw[3 * i + 1] - t.nuc_xyz[3 * I + 1];
+        z = rw[3 * i + 2] - t.nuc_xyz[3 * I + 2];
       }
-      dd[q] = v;
+      v = sqrt(x * x + y * y + z * z);
+      o = (((int64_t)w * L + layer) * d.n_pairs + p) * DZ;
     }
-    __syncthreads();
-    for (int q = threadIdx.x; q < PT * K; q += blockDim.x) {
+    dd[buf * PT + q] = v;
+    oc[buf * PT + q] = o;
+    oe[buf * PT + q] = e;
+  };
+  // this thread's entries of the filter cotangents (rows past the end: zero)
+  TN cw[NJ][kCw];
+  auto request = [&](int64_t row0, int buf) {
+    const int rows = (int)min((int64_t)PT, nrows - row0);
+#pragma unroll
+    for (int k = 0; k < kCw; ++k) {
+      const int q = (int)threadIdx.x + k * NT, row = q / DZ, z = q % DZ;
+      const int64_t o = oc[buf * PT + row] + z;
+      cw[0][k] = ctw[o];
+      if constexpr (JETS) {
+        const int64_t e = oe[buf * PT + row];
+        if (e >= 0) cw[0][k] += ctww[e + z];
+        cw[NJ / 2][k] = ctwd[o];
+        cw[NJ - 1][k] = ctw2[o];
+      }
+#pragma unroll
+      for (int jet = 0; jet < NJ; ++jet) cw[jet][k] = row < rows ? cw[jet][k] : TN(0);
+    }
+  };
+  const int64_t step = (int64_t)gridDim.x * PT;
+  int64_t row0 = (int64_t)blockIdx.x * PT;
+  int buf = 0;
+  if (row0 < nrows) locate(row0, 0);
+  __syncthreads();
+  if (row0 < nrows) request(row0, 0);
+  for (; row0 < nrows; row0 += step, buf ^= 1) {
+    const int rows = (int)min((int64_t)PT, nrows - row0);
+    const double* dc = dd + buf * PT;
+    const bool more = row0 + step < nrows;
+    for (int q = threadIdx.x; q < PT * K; q += NT) {
       const int row = q / K, k = q % K;
       TN e0 = 0, e1 = 0, e2 = 0;
       if (row < rows) {
-        const double dv = dd[row], dm = dv - t.feat_mu[k], sg = t.feat_sig2inv[k];
+        const double dv = dc[row], dm = dv - t.feat_mu[k], sg = t.feat_sig2inv[k];
         const double eg = exp(-dv - dm * dm * sg);
         e0 = (TN)(dv * dv * eg);
         if (JETS) {
@@ -591,112 +637,116 @@ __global__ __launch_bounds__(kThreads) void k_bwd_filter(Dims d, DevTables t, in
         E[(2 * PT + row) * LDK + k] = e2;
       }
     }
-    for (int q = threadIdx.x; q < PT * DZ; q += blockDim.x) {
-      const int row = q / DZ, z = q % DZ;
-      TN v0 = 0, v1 = 0, v2 = 0;
-      if (row < rows) {
-        const int64_t gq = row0 + row, w = gq / np;
-        const int p = p_lo + (int)(gq % np);
-        const int64_t o = ((w * L + layer) * d.n_pairs + p) * DZ + z;
-        v0 = ctw[o];
-        if (JETS) {
-          if (p < d.n_ee) v0 += ctww[((w * L + layer) * d.n_ee + p) * DZ + z];
-          v1 = ctwd[o];
-          v2 = ctw2[o];
-        }
-      }
-      CW[row * LDZ + z] = v0;
-      if (JETS) {
-        CW[(PT + row) * LDZ + z] = v1;
-        CW[(2 * PT + row) * LDZ + z] = v2;
-      }
-    }
-    __syncthreads();
-    for (int jet = 0; jet < NJ; ++jet) {
-      gemm_mfma<TN>(E + jet * PT * LDK, LDK, PT, K, P + Lp.w1W[ch], DZ, U + jet * PT * LDZ, LDZ, false, false);
-      gemm_mfma_wt<TN>(CW + jet * PT * LDZ, LDZ, PT, DZ, P + Lp.w2W[ch], DZ, CU + jet * PT * LDZ, LDZ, false);
-    }
-    __syncthreads();
-    for (int q = threadIdx.x; q < PT * DZ; q += blockDim.x) {
-      const int row = q / DZ, z = q % DZ;
-      const bool ok = row < rows;
-      TN* u0 = U + row * LDZ + z;
-      TN* c0 = CU + row * LDZ + z;
-      const TN u = u0[0] + P[Lp.w1b[ch] + z];
-      const TN s = sig(u);
-      if (!JETS) {
-        c0[0] = ok ? c0[0] * s : TN(0);
-        u0[0] = ok ? ssp(u) : TN(0);  // hidden activation (zero on padding rows)
-      } else {
-        const TN s1 = ssp2(u), s2 = ssp3(u), dv = (TN)dd[row];
-        const TN ud = u0[PT * LDZ], u2 = u0[2 * PT * LDZ], up = dv * ud;
-        const TN ca0 = c0[0], ca1 = c0[PT * LDZ], ca2 = c0[2 * PT * LDZ];
-        c0[0] = ok ? ca0 * s + ca1 * s1 * ud + ca2 * (s1 * u2 + s2 * up * up) : TN(0);
-        c0[PT * LDZ] = ok ? ca1 * s + TN(2) * ca2 * s1 * dv * up : TN(0);
-        c0[2 * PT * LDZ] = ok ? ca2 * s : TN(0);
-        u0[0] = ok ? ssp(u) : TN(0);
-        u0[PT * LDZ] = ok ? s * ud : TN(0);
-        u0[2 * PT * LDZ] = ok ? s * u2 + s1 * up * up : TN(0);
-      }
-    }
-    __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kMaxT; ++k) {
-      const int tt = wv + k * (kThreads / 64);
-      if (tt < nt) {
+    for (int jet = 0; jet < NJ; ++jet)
+#pragma unroll
+      for (int k = 0; k < kCw; ++k) {
+        const int q = (int)threadIdx.x + k * NT;
+        CW[(jet * PT + q / DZ) * LDZ + q % DZ] = cw[jet][k];
+      }
+    if (more) locate(row0 + step, buf ^ 1);
+    __syncthreads();
+    if (more) request(row0 + step, buf ^ 1);
+    // ---- hidden layer: both products, activation and its reverse ----
+#pragma unroll
+    for (int h = 0; h < kHid; ++h) {
+      const int tile = wv + h * NW;
+      if (tile < nh) {
+        const int rt = tile / nz;
+        acc_t cu[NJ], cc[NJ];
 #pragma unroll
         for (int jet = 0; jet < NJ; ++jet) {
-          const TN* X;
-          const TN* Y;
-          int ldx2, a0, b0;
-          if (tt < nt1) {
-            X = E + jet * PT * LDK;
-            ldx2 = LDK;
-            Y = CU + jet * PT * LDZ;
-            a0 = (tt / nz) * 16;
-            b0 = (tt % nz) * 16;
+          TN a[KQ1], c[KQ2];
+          const TN* xr = E + (jet * PT + rt * 16 + c16) * LDK + g * KQ1;
+          const TN* cr = CW + (jet * PT + rt * 16 + c16) * LDZ + g * KQ2;
+#pragma unroll
+          for (int s = 0; s < KQ1; ++s) a[s] = xr[s];
+#pragma unroll
+          for (int s = 0; s < KQ2; ++s) c[s] = cr[s];
+          acc_t z;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) z[v] = TN(0);
+          cu[jet] = MfmaChain<TN, KQ1>::run(a, w1, z, false);
+          cc[jet] = MfmaChain<TN, KQ2>::run(c, w2, z, false);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int row = rt * 16 + MfmaTile<TN>::row_of(lane, v);
+          const bool ok = row < rows;
+          TN* u0 = U + row * LDZ + col;
+          TN* c0 = CU + row * LDZ + col;
+          const TN u = cu[0][v] + b1;
+          const TN s = sig(u);
+          if constexpr (!JETS) {
+            c0[0] = ok ? cc[0][v] * s : TN(0);
+            u0[0] = ok ? ssp(u) : TN(0);  // hidden activation (zero on padding rows)
           } else {
-            X = U + jet * PT * LDZ;
-            ldx2 = LDZ;
-            Y = CW + jet * PT * LDZ;
-            a0 = ((tt - nt1) / nz) * 16;
-            b0 = ((tt - nt1) % nz) * 16;
+            const TN s1 = ssp2(u), s2 = ssp3(u), dv = (TN)dc[row];
+            const TN ud = cu[NJ / 2][v], u2 = cu[NJ - 1][v], up = dv * ud;
+            const TN ca0 = cc[0][v], ca1 = cc[NJ / 2][v], ca2 = cc[NJ - 1][v];
+            // (the fused steps are named: they are part of the FP32 rounding)
+            c0[0] = ok ? fma(ca2, fma(s1, u2, s2 * up * up), fma(ca0, s, ca1 * s1 * ud)) : TN(0);
+            c0[PT * LDZ] = ok ? fma(TN(2) * ca2 * s1 * dv, up, ca1 * s) : TN(0);
+            c0[2 * PT * LDZ] = ok ? ca2 * s : TN(0);
+            u0[0] = ok ? ssp(u) : TN(0);
+            u0[PT * LDZ] = ok ? s * ud : TN(0);
+            u0[2 * PT * LDZ] = ok ? fma(s, u2, s1 * up * up) : TN(0);
           }
+        }
+      }
+    }
+    __syncthreads();
+    // ---- weight gradients dW1 = sum_k E_k^T CU_k and dW2 = sum_k U_k^T CW_k:
+    // every wave keeps its 16 x 16 output tiles in registers across the tiles ----
+#pragma unroll
+    for (int k = 0; k < kTiles; ++k) {
+      const int tt = wv + k * NW;
+      if (tt < nt) {
+        const bool first_mat = tt < nt1;
+        const int a0 = (first_mat ? tt / nz : (tt - nt1) / nz) * 16, b0 = (first_mat ? tt % nz : (tt - nt1) % nz) * 16;
+        const TN* X = (first_mat ? E : U) + a0 + c16;
+        const TN* Y = (first_mat ? CU : CW) + b0 + c16;
+        const int ldx = first_mat ? LDK : LDZ;
+#pragma unroll
+        for (int jet = 0; jet < NJ; ++jet) {
           TN af[RPG], bf[RPG];
 #pragma unroll
           for (int s2 = 0; s2 < RPG; ++s2) {
-            af[s2] = X[(g * RPG + s2) * ldx2 + a0 + c16];
-            bf[s2] = Y[(g * RPG + s2) * LDZ + b0 + c16];
+            af[s2] = X[(jet * PT + g * RPG + s2) * ldx];
+            bf[s2] = Y[(jet * PT + g * RPG + s2) * LDZ];
           }
           accs[k] = MfmaChain<TN, RPG>::run(af, bf, accs[k], false);
         }
       }
     }
-    if (threadIdx.x < DZ) {
-      for (int row = 0; row < rows; ++row) {
-        bacc1 += CU[row * LDZ + threadIdx.x];
-        bacc2 += CW[row * LDZ + threadIdx.x];
+    if (threadIdx.x < 2 * DZ) {
+      const TN* y = (threadIdx.x < DZ ? CU : CW) + threadIdx.x % DZ;
+      for (int r0 = 0; r0 < rows; r0 += 8) {
+        TN v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = y[min(r0 + k, PT - 1) * LDZ];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          if (r0 + k < rows) bacc += v[k];
       }
     }
+    __syncthreads();
   }
   TN* out = fslot + ((size_t)blockIdx.x * L * 3 + blockIdx.y) * fsz;
   // layout of a filter block: [w1W K x DZ][w1b DZ][w2W DZ x DZ][w2b DZ]
 #pragma unroll
-  for (int k = 0; k < kMaxT; ++k) {
-    const int tt = wv + k * (kThreads / 64);
+  for (int k = 0; k < kTiles; ++k) {
+    const int tt = wv + k * NW;
     if (tt < nt) {
       const bool first_mat = tt < nt1;
-      const int a0 = first_mat ? (tt / nz) * 16 : ((tt - nt1) / nz) * 16;
-      const int b0 = first_mat ? (tt % nz) * 16 : ((tt - nt1) % nz) * 16;
+      const int a0 = (first_mat ? tt / nz : (tt - nt1) / nz) * 16, b0 = (first_mat ? tt % nz : (tt - nt1) % nz) * 16;
       const int base = first_mat ? 0 : K * DZ + DZ;
 #pragma unroll
       for (int v = 0; v < 4; ++v) out[base + (a0 + MfmaTile<TN>::row_of(lane, v)) * DZ + b0 + c16] = accs[k][v];
     }
   }
-  if (threadIdx.x < DZ) {
-    out[K * DZ + threadIdx.x] = bacc1;
-    out[K * DZ + DZ + DZ * DZ + threadIdx.x] = bacc2;
-  }
+  if (threadIdx.x < 2 * DZ)
+    out[K * DZ + (threadIdx.x < DZ ? 0 : DZ + DZ * DZ) + threadIdx.x % DZ] = bacc;
 }
 
 template <typename TN>
@@ -786,7 +836,13 @@ static bool bwd_net_arena(const Dims& d) {
   return bwd_net_lds<TN>(d, bwd_wb<TN>(d)) > 160 * 1024;
 }
 
-// rows per tile of k_bwd_filter: 32, or 16 when 32 exceed the LDS
+template <typename TN>
+static size_t bwd_filter_lds(const Dims& d, int PT, bool full) {
+  return (size_t)PT * 48 + (size_t)(full ? 3 : 1) * PT * (ld_pad<TN>(d.K) + 3 * ld_pad<TN>(d.DZ)) * sizeof(TN);
+}
+
+// Rows per tile of k_bwd_filter: 32, or 16 where the row tables of 32 exceed
+// the LDS (the rule is part of the FP32 rounding of the filters' gradients).
 static int bwd_filter_rows(const Dims& d, bool fp32, bool full) {
   const int nj = full ? 3 : 1;
   const size_t tn = fp32 ? sizeof(float) : sizeof(double);
@@ -904,17 +960,37 @@ static void run_backward(const pn_ctx* c, hipStream_t s, int64_t nw, const doubl
   const int64_t max_np = std::max<int64_t>(std::max(n_same, d.n_ee - n_same), (int64_t)d.N * d.NN);
   const int PT = bwd_filter_rows(d, sizeof(TN) == sizeof(float), full);
   const int nb_f = (int)std::min<int64_t>((nw * max_np + PT - 1) / PT, kSlotsFilter);
-  const int nj = full ? 3 : 1;
-  const size_t lds_f = PT * sizeof(double) + (size_t)nj * PT * (ld_pad<TN>(d.K) + 3 * ld_pad<TN>(d.DZ)) * sizeof(TN);
-  auto filt_kernel = PT == 32 ? (full ? &k_bwd_filter<TN, true, 32> : &k_bwd_filter<TN, false, 32>)
-                              : (full ? &k_bwd_filter<TN, true, 16> : &k_bwd_filter<TN, false, 16>);
-  if (lds_f > 65536)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(filt_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)lds_f);
-  hipLaunchKernelGGL(filt_kernel, dim3(nb_f, d.L * 3), dim3(kThreads), lds_f, s, d, c->t, nw, r, P, c->pl, ctw,
-                     full ? reinterpret_cast<const TN*>(ws + L.ctww) : nullptr,
-                     full ? reinterpret_cast<const TN*>(ws + L.ctwd) : nullptr,
-                     full ? reinterpret_cast<const TN*>(ws + L.ctw2) : nullptr, fslot, n_same);
+  const size_t lds_f = bwd_filter_lds<TN>(d, PT, full);
+  auto go = [&](auto kern, int nt) {
+    if (lds_f > 65536)
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds_f);
+    hipLaunchKernelGGL(kern, dim3(nb_f, d.L * 3), dim3(nt), lds_f, s, d, c->t, nw, r, P, c->pl, ctw,
+                       full ? reinterpret_cast<const TN*>(ws + L.ctww) : nullptr,
+                       full ? reinterpret_cast<const TN*>(ws + L.ctwd) : nullptr,
+                       full ? reinterpret_cast<const TN*>(ws + L.ctw2) : nullptr, fslot, n_same);
+  };
+  auto by_rows = [&](auto k1, auto k2) {
+    constexpr int KQ1 = decltype(k1)::value, KQ2 = decltype(k2)::value, nt = KQ2 == 16 ? 512 : 256;
+    if (PT == 32)
+      full ? go(&k_bwd_filter<TN, true, 32, KQ1, KQ2>, nt) : go(&k_bwd_filter<TN, false, 32, KQ1, KQ2>, nt);
+    else
+      full ? go(&k_bwd_filter<TN, true, 16, KQ1, KQ2>, nt) : go(&k_bwd_filter<TN, false, 16, KQ1, KQ2>, nt);
+  };
+  auto by_width = [&](auto k1) {
+    if (d.DZ == 16)
+      by_rows(k1, std::integral_constant<int, 4>());
+    else if (d.DZ == 32)
+      by_rows(k1, std::integral_constant<int, 8>());
+    else  // the accumulators' limit on K and DZ excludes 128
+      by_rows(k1, std::integral_constant<int, 16>());
+  };
+  if (d.K == 16)
+    by_width(std::integral_constant<int, 4>());
+  else if (d.K == 32)
+    by_width(std::integral_constant<int, 8>());
+  else
+    by_width(std::integral_constant<int, 16>());
   const int n_tan = full ? (int)std::min<int64_t>(nw, kSlotsTanAdj) : 0;
   hipLaunchKernelGGL(k_bwd_reduce<TN>, dim3((unsigned)((np + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, d,
                      c->pl, np, nb_net, gslot, nb_f, fslot, n_tan, full ? reinterpret_cast<const TN*>(ws + L.tslot) : nullptr,
@@ -931,12 +1007,8 @@ void launch_backward(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r
 }
 
 size_t backward_filter_lds_bytes(const Dims& d, bool fp32, bool full) {
-  const int nj = full ? 3 : 1;
-  const size_t tn = fp32 ? sizeof(float) : sizeof(double);
-  const size_t ldk = fp32 ? ld_pad<float>(d.K) : ld_pad<double>(d.K);
-  const size_t ldz = fp32 ? ld_pad<float>(d.DZ) : ld_pad<double>(d.DZ);
   const int pt = bwd_filter_rows(d, fp32, full);
-  return pt * sizeof(double) + (size_t)nj * pt * (ldk + 3 * ldz) * tn;
+  return fp32 ? bwd_filter_lds<float>(d, pt, full) : bwd_filter_lds<double>(d, pt, full);
 }
 
 }  // namespace pn
