@@ -29,12 +29,14 @@
 //
 //  k_adj_combine  one wavefront per walker: the per-walker and
 //                 per-determinant cotangents above.
-//  k_adj_slater   one block per (walker, coordinate chunk); the block takes
-//                 the (determinant, spin) pairs one after the other, so every
-//                 accumulation into the backflow cotangents happens in a
-//                 fixed order.
+//  k_adj_slater_16  one block per (walker, coordinate chunk), at most 16
+//                 electrons per spin: a wave per spin.
+//  k_adj_slater   the same for larger spins (or tables): the block takes the
+//                 (determinant, spin) pairs one after the other.
+// Either way every sum into the backflow cotangents has a fixed order.
 #include <math.h>
 
+#include "mfma_gemm.h"
 #include "pn_internal.h"
 
 namespace pn {
@@ -251,6 +253,135 @@ __global__ __launch_bounds__(kThreads) void k_adj_slater(Dims d, DevTables t, in
   for (int q = threadIdx.x; q < N * M; q += blockDim.x) cv[q] = ctv[q];
 }
 
+// Spins of at most 16 electrons.  With G zero-padded to 16 x 16 every product
+// of a (determinant, spin) pair is one 16 x 16 x 16 product on the matrix
+// cores whose operands and results stay in registers (mfma16: a result is the
+// next product's operand), so a pair costs 4 T + 2 of them and no LDS but the
+// table derivatives and the sums.  One wave per spin takes the determinants in
+// order; the sums, products' included, are those of the loops of
+// k_adj_slater, step by step.  Bound by the products (64 cycles per 16 x 16 x 4
+// step, one wave on most SIMDs); the pairs through LDS, two reads per
+// multiply and five barriers, took 20.6 ms instead of 4.9 at 256
+// walkers of the 30-electron diatomic.
+template <int T>
+__global__ __launch_bounds__(128) void k_adj_slater_16(Dims d, DevTables t, int n_chunks,
+                                                       const double* __restrict__ phi,
+                                                       const double* __restrict__ fval,
+                                                       const double* __restrict__ ftan,
+                                                       const double* __restrict__ ginv,
+                                                       const double* __restrict__ ctdet, double* __restrict__ ctftan,
+                                                       double* __restrict__ ctfpart) {
+  extern __shared__ __align__(16) char smem[];
+  const int64_t task = blockIdx.x, w = task / n_chunks;
+  const int chunk = (int)(task % n_chunks);
+  const int N = d.N, M = d.M, P = d.P, N3 = 3 * N;
+  const int a0 = chunk * T, Tc = min(T, N3 - a0), Tp = T + 1;
+  const int lane = threadIdx.x & 63, spin = threadIdx.x >> 6, c16 = lane & 15, g4 = lane >> 4;
+  double* TB = reinterpret_cast<double*>(smem);  // [T + 1][M][N] table derivatives (column T: Laplacian)
+  double* ctT = TB + (size_t)Tp * M * N;         // [T + 1][N][M] cotangents of f tangents (column T: Laplacian)
+  double* ctv = ctT + (size_t)Tp * M * N;        // [N][M] cotangent of f
+  const double* ph = phi + w * N * M * 7;
+  const double* fv = fval + w * N * M;
+  const double* ft = ftan + task * N * Tp * M;
+  for (int q = threadIdx.x; q < Tp * M * N; q += blockDim.x) {
+    const int col = q / (M * N), mu = (q / N) % M, i = q % N;
+    const double* pj = ph + (i * M + mu) * 7;
+    const double f = fv[i * M + mu];
+    double v = 0.0;
+    if (col < Tc) {
+      const int a = a0 + col;
+      v = pj[0] * ft[(i * Tp + col) * M + mu];
+      if (a / 3 == i) v += pj[1 + a % 3] * f;
+    } else if (col == T) {
+      v = pj[0] * ft[(i * Tp + T) * M + mu];
+      for (int c2 = 0; c2 < Tc; ++c2) {
+        const int a = a0 + c2, k = a / 3, al = a % 3;
+        if (k != i) continue;
+        v += pj[4 + al] * f + 2.0 * pj[1 + al] * ft[(i * Tp + c2) * M + mu];
+      }
+    }
+    TB[q] = v;
+  }
+  for (int q = threadIdx.x; q < (Tp + 1) * N * M; q += blockDim.x) ctT[q] = 0.0;
+  __syncthreads();
+  const int n = spin == 0 ? d.n_up : d.n_dn, e0 = spin == 0 ? 0 : d.n_up;
+  const int gsz = d.n_up * d.n_up + d.n_dn * d.n_dn;
+  const int i = e0 + c16;  // this lane's electron (where c16 < n)
+  const v4d z = {0.0, 0.0, 0.0, 0.0};
+  for (int p = 0; p < P && n > 0; ++p) {
+    const int* occ = spin == 0 ? t.det_up + p * d.n_up : t.det_dn + p * d.n_dn;
+    const double* cd = ctdet + (w * P + p) * (N3 + 2);
+    const double cD = cd[N3], cl0 = chunk == 0 ? cd[N3 + 1] : 0.0;
+    const double* Gg = ginv + (w * P + p) * gsz + (spin == 0 ? 0 : d.n_up * d.n_up);
+    double gB[4], gA[4], p0[4];  // G[c16][k], G[k][c16] and phi, k = 4 s + g4
+    int mu[4];                   // orbital of slot k (-1: none)
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int k = 4 * s + g4;
+      const bool ok = c16 < n && k < n;
+      mu[s] = ok ? occ[k] : -1;
+      gB[s] = ok ? Gg[c16 * n + k] : 0.0;
+      gA[s] = ok ? Gg[k * n + c16] : 0.0;
+      p0[s] = ok ? ph[(i * M + mu[s]) * 7] : 0.0;
+    }
+    auto table = [&](int col, double (&tb)[4]) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) tb[s] = mu[s] >= 0 ? TB[(col * M + mu[s]) * N + i] : 0.0;
+    };
+    // transposes, so that lane (electron x = c16) holds slots or rows 4 v + g4:
+    //   M^T = T^T G^T,  (M G)^T = G^T M^T,  (M^2)^T = M^T M^T
+    double tb[4];
+    table(T, tb);
+    v4d q = mfma16(tb, gB, z);  // Q^T, from (G L)^T
+#pragma unroll
+    for (int v = 0; v < 4; ++v) q[v] = fma(-cD, q[v], 4 * v + g4 == c16 ? cl0 : 0.0);
+    v4d mg[T];
+#pragma unroll
+    for (int a = 0; a < T; ++a) {
+      if (a >= Tc) continue;  // wave-uniform
+      table(a, tb);
+      const v4d mt = mfma16(tb, gB, z);
+      mg[a] = mfma16(gA, mt, z);
+      const v4d m2 = mfma16(mfma16(gB, tb, z), mt, z);
+      const double ca = cd[a0 + a];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) q[v] += fma(2.0 * cD, m2[v], -ca * mt[v]);
+    }
+    const v4d cA = mfma16(gA, q, z);  // (Q G)^T
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      if (mu[v] < 0) continue;
+      const double cL = cD * gB[v];
+      const double* pj = ph + (i * M + mu[v]) * 7;
+      double vs = cA[v] * p0[v];
+#pragma unroll
+      for (int col = 0; col < T; ++col) {
+        if (col >= Tc) continue;
+        const int a = a0 + col;
+        const double cT = fma(cd[a], gB[v], -(2.0 * cD * mg[col][v]));
+        double x = cT * p0[v];
+        if (a / 3 == i) {
+          const int al = a % 3;
+          x = fma(2.0 * cL, pj[1 + al], x);
+          vs += fma(cT, pj[1 + al], cL * pj[4 + al]);
+        }
+        ctT[(col * N + i) * M + mu[v]] += x;
+      }
+      double* cl = ctT + (T * N + i) * M + mu[v];
+      *cl = fma(cL, p0[v], *cl);
+      ctv[i * M + mu[v]] += vs;
+    }
+  }
+  __syncthreads();
+  double* co = ctftan + (size_t)task * N * Tp * M;
+  for (int q = threadIdx.x; q < N * Tp * M; q += blockDim.x) {
+    const int e = q / (Tp * M), col = (q / M) % Tp, mu = q % M;
+    co[q] = col < Tc || col == T ? ctT[(col * N + e) * M + mu] : 0.0;
+  }
+  double* cv = ctfpart + (size_t)task * N * M;
+  for (int q = threadIdx.x; q < N * M; q += blockDim.x) cv[q] = ctv[q];
+}
+
 }  // namespace
 
 size_t adj_slater_lds_bytes(const Dims& d, int T) {
@@ -267,6 +398,29 @@ void launch_adj_det(const pn_ctx* c, hipStream_t s, int64_t nw, const WsLayout& 
                      reinterpret_cast<const double*>(ws + L.wdet), reinterpret_cast<const double*>(ws + L.gradf),
                      ct_logabs, ct_grad, ct_lap, ct_eloc, reinterpret_cast<double*>(ws + L.ctc),
                      reinterpret_cast<double*>(ws + L.ctdet));
+  // the matrix-core form where a spin fits a tile (its tables are smaller)
+  const size_t lds16 = (size_t)(2 * (L.T + 1) + 1) * d.M * d.N * sizeof(double);
+  if (std::max(d.n_up, d.n_dn) <= 16) {
+    auto go = [&](auto kern) {
+      if (lds16 > 65536)
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)lds16);
+      hipLaunchKernelGGL(kern, dim3((unsigned)(nw * L.n_chunks)), dim3(128), lds16, s, d, c->t, L.n_chunks,
+                         reinterpret_cast<const double*>(ws + L.phi), reinterpret_cast<const double*>(ws + L.fval),
+                         reinterpret_cast<const double*>(ws + L.ftan), reinterpret_cast<const double*>(ws + L.ginv),
+                         reinterpret_cast<const double*>(ws + L.ctdet), reinterpret_cast<double*>(ws + L.ctftan),
+                         reinterpret_cast<double*>(ws + L.ctfpart));
+    };
+    switch (L.T) {  // the full adjoint's chunks
+      case 1: go(&k_adj_slater_16<1>); return;
+      case 2: go(&k_adj_slater_16<2>); return;
+      case 3: go(&k_adj_slater_16<3>); return;
+      case 4: go(&k_adj_slater_16<4>); return;
+      case 5: go(&k_adj_slater_16<5>); return;
+      case 6: go(&k_adj_slater_16<6>); return;
+      default: break;
+    }
+  }
   const size_t lds = adj_slater_lds_bytes(d, L.T);
   if (lds > 65536)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_adj_slater), hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -425,4 +425,28 @@ __device__ __forceinline__ void gemm_mfma_wt(const TN* X, int ldx, int rows, int
   }
 }
 
+// One wavefront: a 16 x 16 x 16 FP64 product on operands of four values per
+// lane, c[row][col] += sum_k a[row][k] b[k][col]; lane (g, c16) = (l / 16, l %
+// 16) holds row c16 of a and column c16 of b at k = 4 s + g (s = 0..3), and
+// column c16 of c at rows 4 v + g.  A result is therefore the b operand of
+// the next product, and, read as an a operand, its own transpose.  The
+// instruction adds its four products in order of k, each step a fused
+// multiply-add (checked bit for bit on gfx950), so the sum is that of a loop
+// over k = 0 .. 15.
+__device__ __forceinline__ v4d mfma16(const double (&a)[4], const double (&b)[4], v4d c) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], c, 0, 0, 0);
+  return c;
+}
+__device__ __forceinline__ v4d mfma16(const double (&a)[4], v4d b, v4d c) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], c, 0, 0, 0);
+  return c;
+}
+__device__ __forceinline__ v4d mfma16(v4d a, v4d b, v4d c) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], c, 0, 0, 0);
+  return c;
+}
+
 }  // namespace pn
