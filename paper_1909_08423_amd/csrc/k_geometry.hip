@@ -40,6 +40,9 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 
 constexpr int kEG = 8;  // electrons per basis-staging group
 
+// DERIV = false: V, gamma and the orbitals' values only (J = 1 of the 7 jet
+// components, stored at their place in the jet table).
+template <bool DERIV>
 __global__ __launch_bounds__(kThreads) void k_geometry_orbitals(Dims d, DevTables t, const double* __restrict__ r,
                                                                 double* __restrict__ geo, double* __restrict__ phi) {
   extern __shared__ __align__(16) char smem[];
@@ -47,7 +50,8 @@ __global__ __launch_bounds__(kThreads) void k_geometry_orbitals(Dims d, DevTable
   const int N = d.N, NN = d.NN, NB = d.NB, M = d.M;
   double* rs = reinterpret_cast<double*>(smem);   // [N][3]
   double* red = rs + 3 * kMaxElec;                  // [8]
-  double* chi = red + 8;                            // [kEG][NB][7]
+  double* chi = red + 8;                            // [kEG][NB][J]
+  constexpr int J = DERIV ? 7 : 1;
   const double* rw = r + (size_t)w * N * 3;
   for (int k = threadIdx.x; k < 3 * N; k += blockDim.x) rs[k] = rw[k];
   __syncthreads();
@@ -81,7 +85,7 @@ __global__ __launch_bounds__(kThreads) void k_geometry_orbitals(Dims d, DevTable
     gw[3] = 0;
   }
   // --- gamma derivatives per electron coordinate ---
-  for (int q = threadIdx.x; q < 3 * N; q += blockDim.x) {
+  for (int q = threadIdx.x; DERIV && q < 3 * N; q += blockDim.x) {
     int i = q / 3, a = q % 3;
     double g1 = 0, g2 = 0;
     for (int j = 0; j < N; ++j) {
@@ -114,18 +118,18 @@ __global__ __launch_bounds__(kThreads) void k_geometry_orbitals(Dims d, DevTable
                      rs[3 * i + 2] - t.nuc_xyz[3 * C + 2]};
       double r2 = x[0] * x[0] + x[1] * x[1] + x[2] * x[2];
       double g = nrm * exp(-a * r2);
-      double* out = chi + ((size_t)ie * NB + t.shell_first[sh]) * 7;
+      double* out = chi + ((size_t)ie * NB + t.shell_first[sh]) * J;
       if (t.shell_l[sh] == 0) {
         out[0] = g;
-        for (int b = 0; b < 3; ++b) {
+        for (int b = 0; DERIV && b < 3; ++b) {
           out[1 + b] = -2.0 * a * x[b] * g;
           out[4 + b] = (4.0 * a * a * x[b] * x[b] - 2.0 * a) * g;
         }
       } else {
         for (int c = 0; c < 3; ++c) {
-          double* o = out + 7 * c;
+          double* o = out + J * c;
           o[0] = x[c] * g;
-          for (int b = 0; b < 3; ++b) {
+          for (int b = 0; DERIV && b < 3; ++b) {
             double dcb = (b == c) ? 1.0 : 0.0;
             o[1 + b] = (dcb - 2.0 * a * x[c] * x[b]) * g;
             o[4 + b] = (-4.0 * a * dcb * x[b] - 2.0 * a * x[c] + 4.0 * a * a * x[c] * x[b] * x[b]) * g;
@@ -138,11 +142,11 @@ __global__ __launch_bounds__(kThreads) void k_geometry_orbitals(Dims d, DevTable
     for (int q = threadIdx.x; q < ne * M; q += blockDim.x) {
       int ie = q / M, mu = q % M, i = e0 + ie;
       double acc[7] = {0, 0, 0, 0, 0, 0, 0};
-      const double* ch = chi + (size_t)ie * NB * 7;
+      const double* ch = chi + (size_t)ie * NB * J;
       for (int b = 0; b < NB; ++b) {
         double cb = t.mo[(size_t)b * M + mu];
 #pragma unroll
-        for (int k = 0; k < 7; ++k) acc[k] += cb * ch[7 * b + k];
+        for (int k = 0; k < J; ++k) acc[k] += cb * ch[J * b + k];
       }
       if (d.cusp_rc > 0) {
         for (int I = 0; I < NN; ++I) {
@@ -154,9 +158,9 @@ __global__ __launch_bounds__(kThreads) void k_geometry_orbitals(Dims d, DevTable
           // remove the on-centre s part
           for (int k = t.s_first[I]; k < t.s_first[I + 1]; ++k) {
             double cb = t.mo[(size_t)t.s_basis[k] * M + mu];
-            const double* cs = ch + 7 * t.s_basis[k];
+            const double* cs = ch + J * t.s_basis[k];
 #pragma unroll
-            for (int m = 0; m < 7; ++m) acc[m] -= cb * cs[m];
+            for (int m = 0; m < J; ++m) acc[m] -= cb * cs[m];
           }
           // add sign * exp(p(rho)) as a radial function
           const double* al = t.cusp_alpha + ((size_t)I * M + mu) * 5;
@@ -177,7 +181,7 @@ __global__ __launch_bounds__(kThreads) void k_geometry_orbitals(Dims d, DevTable
       }
       double* o = phw + ((size_t)i * M + mu) * 7;
 #pragma unroll
-      for (int k = 0; k < 7; ++k) o[k] = acc[k];
+      for (int k = 0; k < J; ++k) o[k] = acc[k];
     }
   }
 }
@@ -185,10 +189,11 @@ __global__ __launch_bounds__(kThreads) void k_geometry_orbitals(Dims d, DevTable
 }  // namespace
 
 void launch_geometry_orbitals(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r, char* ws,
-                              const WsLayout& L) {
+                              const WsLayout& L, bool derivs) {
   const Dims& d = c->d;
-  size_t lds = (3 * kMaxElec + 8 + (size_t)kEG * d.NB * 7) * sizeof(double);
-  hipLaunchKernelGGL(k_geometry_orbitals, dim3((unsigned)nw), dim3(kThreads), lds, s, d, c->t, r,
+  size_t lds = (3 * kMaxElec + 8 + (size_t)kEG * d.NB * (derivs ? 7 : 1)) * sizeof(double);
+  auto kern = derivs ? &k_geometry_orbitals<true> : &k_geometry_orbitals<false>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)nw), dim3(kThreads), lds, s, d, c->t, r,
                      reinterpret_cast<double*>(ws + L.geo), reinterpret_cast<double*>(ws + L.phi));
 }
 

@@ -891,7 +891,7 @@ pn_status eval_impl(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r,
     const int64_t n = std::min<int64_t>(L.tile, nw - w0);
     const double* rt = r + w0 * d.N * 3;
     clk.begin(1);
-    launch_geometry_orbitals(c, s, n, rt, base, L);
+    launch_geometry_orbitals(c, s, n, rt, base, L, derivs);
     clk.end(1);
     if (no_net) {
       // neither Jastrow factor nor backflow: f = 1, J = 0 and no network work
@@ -980,7 +980,7 @@ pn_status pn_eval_backward(const pn_ctx* c, hipStream_t s, int64_t nw, const dou
   for (int64_t w0 = 0; w0 < nw; w0 += L.tile) {
     const int64_t n = std::min<int64_t>(L.tile, nw - w0);
     const double* rt = r + w0 * d.N * 3;
-    launch_geometry_orbitals(c, s, n, rt, base, L);
+    launch_geometry_orbitals(c, s, n, rt, base, L, full);
     if (fp64) {
       launch_filters<double>(c, s, n, rt, static_cast<const double*>(P), base, L, full);
       launch_net_value<double>(c, s, n, static_cast<const double*>(P), base, L);
@@ -1043,7 +1043,7 @@ pn_status pn_eval_backward_cusp(const pn_ctx* c, hipStream_t s, int64_t nw, cons
   for (int64_t w0 = 0; w0 < nw; w0 += L.tile) {
     const int64_t n = std::min<int64_t>(L.tile, nw - w0);
     const double* rt = r + w0 * d.N * 3;
-    launch_geometry_orbitals(c, s, n, rt, base, L);
+    launch_geometry_orbitals(c, s, n, rt, base, L, false);
     if (no_net) {
       launch_fill(s, n * d.N * d.M, reinterpret_cast<double*>(base + L.fval), 1.0);
       launch_fill(s, n, reinterpret_cast<double*>(base + L.jval), 0.0);

@@ -222,7 +222,7 @@ __host__ __device__ constexpr int ld_pad(int D) {
 // Launchers implemented in the kernel translation units.
 namespace pn {
 void launch_geometry_orbitals(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r, char* ws,
-                              const WsLayout& L);
+                              const WsLayout& L, bool derivs);
 template <typename TN>
 void launch_filters(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r, const TN* P, char* ws,
                     const WsLayout& L, bool jets);
