@@ -283,12 +283,40 @@ __host__ __device__ inline LrLds lr_lds(const Dims& d, int T) {
   return o;
 }
 
+// NB: the spins' largest electron number where it is at most 8 (4 stands for
+// less): an item of steps 2 and 3 is then one row with all its slots, sums in
+// registers, every operand requested before the first is used.  NB = 0 for
+// larger spins: kSL consecutive slots of one row.
 // WIDE: spins of 8 or more electrons, blocks of over 40 KB of LDS (at most
-// two per CU, so a wave may hold up to 256 registers): slot blocking in
-// steps 2 and 3 and the next chunk's tangents of the first 8 step-1 items
-// requested ahead.  Otherwise one slot per item, no prefetch, and at most
-// 128 registers (four blocks per CU).
-template <bool WIDE>
+// two per CU, so a wave may hold up to 256 registers): the next chunk's
+// tangents of the first kItems step-1 items requested a chunk ahead.
+// Otherwise at most 128 registers (four blocks per CU), requested at the start of the step.
+//
+// At these sizes (ten electrons, 16 members: 20 k multiply-adds per chunk) a
+// block waits for latency, not for arithmetic: what counts is the number of
+// dependent LDS and cache round trips between two barriers and the index
+// arithmetic around them, so there is no runtime division in the chunk loop,
+// the Laplacian's terms of a coordinate's own electron are items of their own
+// (among the others they held every wave up), the sums over rows and members
+// run on as many lanes as they have terms instead of a wave each, and members
+// replacing at most two orbitals of a spin work on 2 x 2 blocks.  Measured
+// against the form without these: 4096 walkers of ten electrons with 16
+// members 0.50 -> 0.20 ms, 1001 of them 0.138 -> 0.080 ms, 2048 of seven
+// electrons 0.151 -> 0.100 ms, a launch of the 30-electron diatomic's large
+// batch with 64 members 3.6 -> 2.35 ms.
+constexpr int kSL = 4;
+constexpr int kItems = 8;  // step-1 items per thread with their tangents in registers
+
+// The sum over the 64 lanes of a wave whose lanes from width on hold zeros,
+// in the order of the full butterfly.
+__device__ __forceinline__ double sum_lanes(double v, int width) {
+  for (int off = width >> 1; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+__device__ __forceinline__ int pow2_lanes(int n) { return n <= 1 ? 1 : min(64, 1 << (32 - __builtin_clz((unsigned)(n - 1)))); }
+
+// KX: members replace at most KX orbitals of a spin (2 or kMaxExc).
+template <int NB, bool WIDE, int KX>
 __global__ __launch_bounds__(kThreads, WIDE ? 2 : 4) void k_lr_tangent(Dims d, DevTables t, int64_t nw, int T, int n_chunks,
                                                          const double* __restrict__ geo,
                                                          const double* __restrict__ phi,
@@ -306,7 +334,8 @@ __global__ __launch_bounds__(kThreads, WIDE ? 2 : 4) void k_lr_tangent(Dims d, D
   if (w >= nw || (flag[2 * w] | flag[2 * w + 1])) return;  // the direct path takes this walker
   const LrLds o = lr_lds(d, T);
   const int N = d.N, M = d.M, P = d.P, nu = d.n_up, nd = d.n_dn;
-  const int tid = threadIdx.x, nth = blockDim.x;
+  const int tid = threadIdx.x;
+  constexpr int nth = kThreads;
   double* G0s = sm + o.G0;
   double* THs = sm + o.TH;
   double* TB = sm + o.TB;      // [T][N][M] table derivatives of the chunk (orbital fastest)
@@ -354,197 +383,286 @@ __global__ __launch_bounds__(kThreads, WIDE ? 2 : 4) void k_lr_tangent(Dims d, D
     PF[q] = phi[((size_t)w * N * M + q) * 7];
     PF[N * M + q] = fval[(size_t)w * N * M + q];
   }
+  // offsets of Xi[v][h] in a spin's rows, in the third row of the member's
+  // inverse (an identity row that nothing reads)
+  if constexpr (KX == 2) {
+    __syncthreads();
+    for (int q = tid; q < 2 * P; q += nth) {
+      const int s = q & 1, n = ns(s), k = t.lr_k[q];
+      int* off = reinterpret_cast<int*>(DI + q * kMaxExc * kMaxExc + 2 * kMaxExc);
+      for (int j = 0; j < 2; ++j)
+        for (int l = 0; l < 2; ++l)
+          off[2 * j + l] = (j < k && l < k) ? (n + t.lr_part[q * kMaxExc + j]) * n + t.lr_hole[q * kMaxExc + l] : -1;
+    }
+  }
   __syncthreads();
 
   const double* ph = phi + w * N * M * 7;
-  const double* fv = fval + w * N * M;
   const double* g = geo + w * kGeoStride(N);
   const int Tp = T + 1, NTM = N * Tp * M;
-  // the first chunk's tangents of the step-1 items held in registers, and
-  // the items' (i, column, mu) decoded once (the same in every chunk; M <= 128
-  // and columns <= 17 fit their 8-bit fields)
-  constexpr int kItems = WIDE ? 8 : 1;  // step-1 items per thread kept in registers
+  // the items' (i, column, mu) of step 1, the same in every chunk: those of the
+  // first kItems decoded once (M <= 128 and columns <= 17 fit their 8-bit
+  // fields), the others' from the last by adding nth in these digits
+  constexpr int kHeld = WIDE ? kItems : 0;
   double ftv[kItems];
   int pk[kItems];
+  const int nth_i = nth / (Tp * M), nth_c = (nth / M) % Tp, nth_m = nth % M;
+  auto advance = [&](int& i, int& col, int& mu) {
+    mu += nth_m;
+    col += nth_c;
+    i += nth_i;
+    if (mu >= M) {
+      mu -= M;
+      ++col;
+    }
+    if (col >= Tp) {
+      col -= Tp;
+      ++i;
+    }
+  };
+  int i8, c8, m8;  // the item after the last of pk
+  {
+    int i = tid / (Tp * M), col = (tid / M) % Tp, mu = tid % M;
 #pragma unroll
-  for (int u = 0; u < kItems; ++u) {
-    const int q = tid + u * nth;
-    if (q >= NTM) break;
-    ftv[u] = ftan[(size_t)w * n_chunks * NTM + q];
-    pk[u] = ((q / (Tp * M)) << 16) | (((q / M) % Tp) << 8) | (q % M);
+    for (int u = 0; u < kHeld; ++u) {
+      pk[u] = (i << 16) | (col << 8) | mu;
+      advance(i, col, mu);
+    }
+    i8 = i;
+    c8 = col;
+    m8 = mu;
   }
+  auto request = [&](const double* f) {
+#pragma unroll
+    for (int u = 0; u < kItems; ++u) ftv[u] = f[min(tid + u * nth, NTM - 1)];
+  };
+  if constexpr (WIDE) request(ftan + (size_t)w * n_chunks * NTM);
+  // the (column, row) that a thread starts with in steps 2 and 3
+  const int nr2 = NB ? o.R0 + o.R1 : o.R0 * ((nu + kSL - 1) / kSL) + o.R1 * ((nd + kSL - 1) / kSL);
+  const int nr3 = NB ? d.nv[0] + d.nv[1] : d.nv[0] * ((nu + kSL - 1) / kSL) + d.nv[1] * ((nd + kSL - 1) / kSL);
+  const int col2 = tid / nr2, rem2 = tid - col2 * nr2;
+  const int col3 = nr3 ? tid / nr3 : 0, rem3 = tid - col3 * nr3;
+  const int nmx = max(nu, nd), lanes_n = pow2_lanes(nmx), lanes_p = pow2_lanes(P);
   for (int chunk = 0; chunk < n_chunks; ++chunk) {
     const int a0 = chunk * T, Tc = min(T, 3 * N - a0);
     const double* ft = ftan + ((size_t)w * n_chunks + chunk) * NTM;
     const double* jt = jtan + ((size_t)w * n_chunks + chunk) * Tp;
     // 1. table derivatives T_a[mu][i] and the chunk's part of the table
-    //    Laplacian, read in the memory order of the network tangents.  A
-    //    thread's items (i, column, mu) are the same in every chunk: phi
-    //    and f come from LDS (copied once per walker), and the tangents of
-    //    the first kItems items for the next chunk are requested into
-    //    registers at the end of this step, so the HBM latency overlaps
-    //    steps 2 to 5.
+    //    Laplacian, the former read in the memory order of the network
+    //    tangents
     {
+      auto put = [&](int i, int col, int mu, double f) {  // coordinates of other electrons
+        if (col < Tc && (unsigned)(a0 + col - 3 * i) >= 3u) TB[(col * N + i) * M + mu] = PF[i * M + mu] * f;
+      };
 #pragma unroll
-      for (int u = 0; u < kItems; ++u) {
-        const int q = tid + u * nth;
-        if (q >= NTM) break;
-        const int i = pk[u] >> 16, col = (pk[u] >> 8) & 255, mu = pk[u] & 255;
-        const double* pj = ph + ((size_t)i * M + mu) * 7;
-        const double f = PF[N * M + i * M + mu];
-        if (col < Tc) {
-          const int a = a0 + col, k = a / 3, al = a % 3;
-          double v = PF[i * M + mu] * ftv[u];
-          if (k == i) v += pj[1 + al] * f;
-          TB[((size_t)col * N + i) * M + mu] = v;
-        } else if (col == T) {
-          double v = PF[i * M + mu] * ftv[u];
-          for (int c2 = 0; c2 < Tc; ++c2) {
-            const int a = a0 + c2, k = a / 3, al = a % 3;
-            if (k != i) continue;
-            v += pj[4 + al] * f + 2.0 * pj[1 + al] * ft[((size_t)i * Tp + c2) * M + mu];
-          }
-          LT[mu * N + i] += v;
-        }
+      for (int u = 0; u < kHeld; ++u) {
+        if (tid + u * nth < NTM) put(pk[u] >> 16, (pk[u] >> 8) & 255, pk[u] & 255, ftv[u]);
       }
-      for (int q = tid + kItems * nth; q < NTM; q += nth) {  // items past the register-resident ones
-        const int i = q / (Tp * M), col = (q / M) % Tp, mu = q % M;
-        const double* pj = ph + ((size_t)i * M + mu) * 7;
-        const double f = fv[i * M + mu];
-        if (col < Tc) {
-          const int a = a0 + col, k = a / 3, al = a % 3;
-          double v = pj[0] * ft[q];
-          if (k == i) v += pj[1 + al] * f;
-          TB[((size_t)col * N + i) * M + mu] = v;
-        } else if (col == T) {
-          double v = pj[0] * ft[q];
-          for (int c2 = 0; c2 < Tc; ++c2) {
-            const int a = a0 + c2, k = a / 3, al = a % 3;
-            if (k != i) continue;
-            v += pj[4 + al] * f + 2.0 * pj[1 + al] * ft[((size_t)i * Tp + c2) * M + mu];
-          }
-          LT[mu * N + i] += v;
-        }
-      }
-      if (chunk + 1 < n_chunks) {
-        const double* ftn = ft + (size_t)NTM;  // the next chunk's tangents follow this chunk's
+      int i = i8, col = c8, mu = m8;
+      for (int q = tid + kHeld * nth; q < NTM; q += kItems * nth) {
+        double f[kItems];
+#pragma unroll
+        for (int u = 0; u < kItems; ++u) f[u] = ft[min(q + u * nth, NTM - 1)];
 #pragma unroll
         for (int u = 0; u < kItems; ++u) {
-          const int q = tid + u * nth;
-          if (q >= NTM) break;
-          ftv[u] = ftn[q];
+          if (q + u * nth < NTM) put(i, col, mu, f[u]);
+          advance(i, col, mu);
         }
+      }
+      for (int q = tid; q < N * M; q += nth) {  // an electron's own coordinates, and the Laplacian
+        const int i = q / M, mu = q - i * M;
+        const double* pj = ph + (size_t)q * 7;
+        const double* fi = ft + (size_t)i * Tp * M + mu;
+        const double p0 = PF[q], f = PF[N * M + q];
+        double v = p0 * fi[(size_t)T * M];
+#pragma unroll
+        for (int al = 0; al < 3; ++al) {
+          const int c = 3 * i + al - a0;
+          if ((unsigned)c >= (unsigned)Tc) continue;
+          const double fc = fi[(size_t)c * M];
+          TB[(c * N + i) * M + mu] = fma(pj[1 + al], f, p0 * fc);
+          v += fma(pj[4 + al], f, 2.0 * pj[1 + al] * fc);
+        }
+        LT[mu * N + i] += v;
+      }
+      if constexpr (WIDE) {
+        if (chunk + 1 < n_chunks) request(ft + NTM);  // the next chunk's tangents follow this chunk's
       }
     }
     __syncthreads();
-    // 2. B_a = T_a G_0 on the first determinant's rows and the virtual rows;
-    //    an item is SL consecutive slots k of one row (independent sums
-    //    sharing the row's reads; SL = 4 from 8 electrons of a spin on)
-    auto step2 = [&](auto sl_tag) {
-      constexpr int SL = decltype(sl_tag)::value;
-      const int nq0 = o.R0 * ((nu + SL - 1) / SL), nq1 = o.R1 * ((nd + SL - 1) / SL), nq = nq0 + nq1;
-      for (int q = tid; q < Tc * nq; q += nth) {
-        const int col = q / nq, rem = q % nq;
-        const int s = rem >= nq0, rq = rem - (s ? nq0 : 0), n = ns(s), nks = (n + SL - 1) / SL;
-        const int r = rq / nks, k0 = (rq % nks) * SL;
-        const double* tb = TB + ((size_t)col * N + e0s(s)) * M + ROWORB[s * o.R0 + r];
-        const double* Gs = G0s + (s ? nu * nu : 0);
-        double acc[SL];
-#pragma unroll
-        for (int u = 0; u < SL; ++u) acc[u] = 0.0;
-        for (int i = 0; i < n; ++i) {
-          const double x = tb[i * M];
-#pragma unroll
-          for (int u = 0; u < SL; ++u) acc[u] += x * Gs[i * n + min(k0 + u, n - 1)];
-        }
-        double* B = BM + (size_t)col * bsz + soffB(s) + r * n;
-#pragma unroll
-        for (int u = 0; u < SL; ++u)
-          if (k0 + u < n) B[k0 + u] = acc[u];
-      }
-    };
-    if constexpr (WIDE)
-      step2(std::integral_constant<int, 4>());
-    else
-      step2(std::integral_constant<int, 1>());
-    __syncthreads();
-    // 3. Xi_a = B_a - Theta N_a on the virtual rows (in place; an item is
-    //    SL consecutive slots of one row, as in step 2), and tr N_a, tr N_a^2 per
-    //    (coordinate, spin) by one wavefront (lane k: row k), summed across
-    //    the lanes in a fixed order
+    // 2. B_a = T_a G_0 on the first determinant's rows and the virtual rows
     {
-      auto xi = [&](auto sl_tag) {
-        constexpr int SL = decltype(sl_tag)::value;
-        const int nq0 = d.nv[0] * ((nu + SL - 1) / SL), nq1 = d.nv[1] * ((nd + SL - 1) / SL), nq = nq0 + nq1;
-        for (int q = tid; q < Tc * nq; q += nth) {
-          const int col = q / nq, rem = q % nq;
-          const int s = rem >= nq0, rq = rem - (s ? nq0 : 0), n = ns(s), nks = (n + SL - 1) / SL;
-          const int v = rq / nks, k0 = (rq % nks) * SL;
-          double* B = BM + (size_t)col * bsz + soffB(s);
-          const double* th = THs + soffT(s) + v * n;
-          double acc[SL];
+      int col = col2, rem = rem2;
+      for (; col < Tc;) {
+        if constexpr (NB > 0) {
+          const int s = rem >= o.R0, n = ns(s);
+          const double* tb = TB + (col * N + e0s(s)) * M + ROWORB[rem];
+          const double* Gs = G0s + (s ? nu * nu : 0);
+          double* B = BM + col * bsz + soffB(s) + (rem - (s ? o.R0 : 0)) * n;
+          double x[NB], acc[NB];
 #pragma unroll
-          for (int u = 0; u < SL; ++u) acc[u] = B[(n + v) * n + min(k0 + u, n - 1)];
+          for (int i = 0; i < NB; ++i) {
+            x[i] = i < n ? tb[i * M] : 0.0;
+            acc[i] = 0.0;
+          }
+#pragma unroll
+          for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int k = 0; k < NB; ++k)
+              if (i < n && k < n) acc[k] += x[i] * Gs[i * n + k];
+#pragma unroll
+          for (int k = 0; k < NB; ++k)
+            if (k < n) B[k] = acc[k];
+        } else {
+          const int nq0 = o.R0 * ((nu + kSL - 1) / kSL);
+          const int s = rem >= nq0, rq = rem - (s ? nq0 : 0), n = ns(s), nks = (n + kSL - 1) / kSL;
+          const int r = rq / nks, k0 = (rq - r * nks) * kSL;
+          const double* tb = TB + (col * N + e0s(s)) * M + ROWORB[s * o.R0 + r];
+          const double* Gs = G0s + (s ? nu * nu : 0);
+          double acc[kSL];
+#pragma unroll
+          for (int u = 0; u < kSL; ++u) acc[u] = 0.0;
+          for (int i = 0; i < n; ++i) {
+            const double x = tb[i * M];
+#pragma unroll
+            for (int u = 0; u < kSL; ++u) acc[u] += x * Gs[i * n + min(k0 + u, n - 1)];
+          }
+          double* B = BM + col * bsz + soffB(s) + r * n;
+#pragma unroll
+          for (int u = 0; u < kSL; ++u)
+            if (k0 + u < n) B[k0 + u] = acc[u];
+        }
+        for (rem += nth; rem >= nr2; rem -= nr2) ++col;
+      }
+    }
+    __syncthreads();
+    // 3. Xi_a = B_a - Theta N_a on the virtual rows (in place), and tr N_a,
+    //    tr N_a^2 per (coordinate, spin), a lane per row, summed across the
+    //    lanes in a fixed order
+    {
+      int col = col3, rem = rem3;
+      for (; nr3 > 0 && col < Tc;) {
+        if constexpr (NB > 0) {
+          const int s = rem >= d.nv[0], n = ns(s), v = rem - (s ? d.nv[0] : 0);
+          double* B = BM + col * bsz + soffB(s);
+          const double* th = THs + soffT(s) + v * n;
+          double x[NB], acc[NB];
+#pragma unroll
+          for (int k = 0; k < NB; ++k) {
+            x[k] = k < n ? th[k] : 0.0;
+            acc[k] = k < n ? B[(n + v) * n + k] : 0.0;
+          }
+#pragma unroll
+          for (int l = 0; l < NB; ++l)
+#pragma unroll
+            for (int k = 0; k < NB; ++k)
+              if (l < n && k < n) acc[k] -= x[l] * B[l * n + k];
+#pragma unroll
+          for (int k = 0; k < NB; ++k)
+            if (k < n) B[(n + v) * n + k] = acc[k];
+        } else {
+          const int nq0 = d.nv[0] * ((nu + kSL - 1) / kSL);
+          const int s = rem >= nq0, rq = rem - (s ? nq0 : 0), n = ns(s), nks = (n + kSL - 1) / kSL;
+          const int v = rq / nks, k0 = (rq - v * nks) * kSL;
+          double* B = BM + col * bsz + soffB(s);
+          const double* th = THs + soffT(s) + v * n;
+          double acc[kSL];
+#pragma unroll
+          for (int u = 0; u < kSL; ++u) acc[u] = B[(n + v) * n + min(k0 + u, n - 1)];
           for (int l = 0; l < n; ++l) {
             const double x = th[l];
 #pragma unroll
-            for (int u = 0; u < SL; ++u) acc[u] -= x * B[l * n + min(k0 + u, n - 1)];
+            for (int u = 0; u < kSL; ++u) acc[u] -= x * B[l * n + min(k0 + u, n - 1)];
           }
 #pragma unroll
-          for (int u = 0; u < SL; ++u)
+          for (int u = 0; u < kSL; ++u)
             if (k0 + u < n) B[(n + v) * n + k0 + u] = acc[u];
         }
-      };
-      if constexpr (WIDE)
-        xi(std::integral_constant<int, 4>());
-      else
-        xi(std::integral_constant<int, 1>());
-      const int lane = tid & 63, wv = tid >> 6, nwv = nth >> 6;
-      for (int cs = wv; cs < Tc * 2; cs += nwv) {
-        const int col = cs / 2, s = cs % 2, n = ns(s);
-        const double* B = BM + (size_t)col * bsz + soffB(s);
+        for (rem += nth; rem >= nr3; rem -= nr3) ++col;
+      }
+      const int sh = log2_of(lanes_n), lane = tid & (lanes_n - 1);
+      for (int cs = tid >> sh; cs < ((Tc * 2 + (nth >> sh) - 1) & ~((nth >> sh) - 1)); cs += nth >> sh) {
+        const int col = min(cs >> 1, Tc - 1), s = cs & 1, n = ns(s);
+        const double* B = BM + col * bsz + soffB(s);
         double tr = 0.0, tr2 = 0.0;
         if (lane < n) {
           tr = B[lane * n + lane];
+#pragma unroll 4
           for (int l = 0; l < n; ++l) tr2 += B[lane * n + l] * B[l * n + lane];
         }
-        for (int off = 32; off > 0; off >>= 1) {
-          tr += __shfl_xor(tr, off, 64);
-          tr2 += __shfl_xor(tr2, off, 64);
-        }
-        if (lane == 0) {
-          TRN[col * 2 + s] = tr;
-          TRN2[col * 2 + s] = tr2;
+        tr = sum_lanes(tr, lanes_n);
+        tr2 = sum_lanes(tr2, lanes_n);
+        if (lane == 0 && cs < Tc * 2) {
+          TRN[cs] = tr;
+          TRN2[cs] = tr2;
         }
       }
     }
     __syncthreads();
     // 4. S += sum_a Xi_a N_a (virtual rows x all slots), and per member
-    //    d_a ln|D_p| and tr((D_p^-1 Xi_a)^2)
-    for (int q = tid; q < thsz + 2 * P; q += nth) {
-      if (q < thsz) {
+    //    d_a ln|D_p| = tr(D_p^-1 Xi_a[v][h]) and tr((D_p^-1 Xi_a[v][h])^2),
+    //    members from the next whole wave on
+    const int th64 = (thsz + 63) & ~63;
+    for (int q = tid; q < th64 + 2 * P; q += nth) {
+      if (q < th64) {
+        if (q >= thsz) continue;
         const int s = q >= sT1, rr = q - soffT(s), n = ns(s);
-        const int v = rr / n, h = rr % n;
+        const int v = rr / n, h = rr - v * n;
         double acc = SS[q];
         for (int col = 0; col < Tc; ++col) {
-          const double* B = BM + (size_t)col * bsz + soffB(s);
-          for (int k = 0; k < n; ++k) acc += B[(n + v) * n + k] * B[k * n + h];
+          const double* B = BM + col * bsz + soffB(s);
+          if constexpr (NB > 0) {
+            double x[NB], y[NB];
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+              if (k < n) {
+                x[k] = B[(n + v) * n + k];
+                y[k] = B[k * n + h];
+              }
+            }
+#pragma unroll
+            for (int k = 0; k < NB; ++k)
+              if (k < n) acc += x[k] * y[k];
+          } else {
+#pragma unroll 4
+            for (int k = 0; k < n; ++k) acc += B[(n + v) * n + k] * B[k * n + h];
+          }
         }
         SS[q] = acc;
+        continue;
+      }
+      const int ps = q - th64, p = ps >> 1, s = ps & 1, n = ns(s);
+      const double* Di = DI + ps * kMaxExc * kMaxExc;
+      double qsum = QACC[ps];
+      if constexpr (KX == 2) {
+        const int* off = reinterpret_cast<const int*>(Di + 2 * kMaxExc);
+        const int o00 = off[0], o01 = off[1], o10 = off[2], o11 = off[3];
+        const double d00 = Di[0], d01 = Di[1], d10 = Di[kMaxExc], d11 = Di[kMaxExc + 1];
+#pragma unroll 3
+        for (int col = 0; col < Tc; ++col) {
+          double gp = 0.0;
+          if (o00 >= 0) {
+            const double* B = BM + col * bsz + soffB(s);
+            const double x00 = B[o00], x01 = o01 >= 0 ? B[o01] : 0.0, x10 = o10 >= 0 ? B[o10] : 0.0,
+                         x11 = o11 >= 0 ? B[o11] : 0.0;
+            const double m00 = fma(d01, x10, d00 * x00), m01 = fma(d01, x11, d00 * x01);
+            const double m10 = fma(d11, x10, d10 * x00), m11 = fma(d11, x11, d10 * x01);
+            gp = m00 + m11;
+            qsum = fma(m00, m00, qsum);
+            qsum = fma(m01, m10, qsum);
+            qsum = fma(m10, m01, qsum);
+            qsum = fma(m11, m11, qsum);
+          }
+          GPA[(p * T + col) * 2 + s] = gp;
+        }
       } else {
-        // member p, spin s: d_a ln|det D_p| = tr(D^-1 Xi_a[v][h]) and
-        // tr((D^-1 Xi_a[v][h])^2) for the chunk's coordinates
-        const int p = (q - thsz) >> 1, s = (q - thsz) & 1;
-        const int k = t.lr_k[p * 2 + s];
-        double qsum = QACC[p * 2 + s];
-        const int n = ns(s);
-        const int* hl = t.lr_hole + (p * 2 + s) * kMaxExc;
-        const int* pt = t.lr_part + (p * 2 + s) * kMaxExc;
-        const double* Di = DI + (p * 2 + s) * kMaxExc * kMaxExc;
+        const int k = t.lr_k[ps];
+        const int* hl = t.lr_hole + ps * kMaxExc;
+        const int* pt = t.lr_part + ps * kMaxExc;
         for (int col = 0; col < Tc; ++col) {
           double gp = 0.0;
           if (k > 0) {
-            const double* B = BM + (size_t)col * bsz + soffB(s);
+            const double* B = BM + col * bsz + soffB(s);
             double X[kMaxExc][kMaxExc], Mx[kMaxExc][kMaxExc];
 #pragma unroll
             for (int j = 0; j < kMaxExc; ++j)
@@ -568,50 +686,49 @@ __global__ __launch_bounds__(kThreads, WIDE ? 2 : 4) void k_lr_tangent(Dims d, D
           }
           GPA[(p * T + col) * 2 + s] = gp;
         }
-        QACC[p * 2 + s] = qsum;
       }
+      QACC[ps] = qsum;
     }
     __syncthreads();
-    // 5. determinant sum per coordinate (one wavefront per coordinate, lanes
-    //    over members, summed across the lanes in a fixed order), gamma and J
+    // 5. determinant sum per coordinate (lanes over members, summed across
+    //    the lanes in a fixed order), gamma and J
     {
-      const int lane = tid & 63, wv = tid >> 6, nwv = nth >> 6;
-      for (int col = wv; col < Tc; col += nwv) {
-        const int a = a0 + col, k = a / 3, al = a % 3;
+      const int sh = log2_of(lanes_p), lane = tid & (lanes_p - 1), cols = nth >> sh;
+      for (int c = tid >> sh; c < (Tc + cols - 1) / cols * cols; c += cols) {
+        const int col = min(c, Tc - 1), a = a0 + col, k = a / 3, al = a - 3 * k;
         const double trn = TRN[col * 2] + TRN[col * 2 + 1];
+        double gj = 0.0, gl = 0.0, jc = 0.0;
+        if (lane == 0) {
+          gj = g[4 + 6 * k + al];
+          gl = g[4 + 6 * k + 3 + al];
+          jc = jt[col];
+        }
         double dpsi = 0.0, wsq = 0.0;
         for (int p = lane; p < P; p += 64) {
           const double gp = trn + GPA[(p * T + col) * 2] + GPA[(p * T + col) * 2 + 1];
           dpsi += WD[p] * gp;
           wsq += WD[p] * gp * gp;
         }
-        for (int off = 32; off > 0; off >>= 1) {
-          dpsi += __shfl_xor(dpsi, off, 64);
-          wsq += __shfl_xor(wsq, off, 64);
-        }
-        if (lane == 0) {
-          const double gtot = g[4 + 6 * k + al] + jt[col] + dpsi;
+        dpsi = sum_lanes(dpsi, lanes_p);
+        wsq = sum_lanes(wsq, lanes_p);
+        if (lane == 0 && c < Tc) {
+          const double gtot = gj + jc + dpsi;
           grad[w * N * 3 + a] = gtot;
-          LAPC[col] = wsq - dpsi * dpsi + g[4 + 6 * k + 3 + al];
+          LAPC[col] = wsq - dpsi * dpsi + gl;
           SQC[col] = gtot * gtot;
         }
       }
     }
     __syncthreads();
-    if (tid == 0) {
-      double lap = SCAL[0], sq = SCAL[1], t2u = SCAL[2], t2d = SCAL[3];
-      for (int col = 0; col < Tc; ++col) {
-        lap += LAPC[col];
-        sq += SQC[col];
-        t2u += TRN2[col * 2];
-        t2d += TRN2[col * 2 + 1];
-      }
-      SCAL[0] = lap + jt[T];
-      SCAL[1] = sq;
-      SCAL[2] = t2u;
-      SCAL[3] = t2d;
+    if (tid < 4) {  // lap, |grad|^2, sum tr N^2 of either spin
+      const double* x = tid == 0 ? LAPC : (tid == 1 ? SQC : TRN2 + (tid - 2));
+      const int step = tid < 2 ? 1 : 2;
+      double acc = SCAL[tid];
+#pragma unroll 4
+      for (int col = 0; col < Tc; ++col) acc += x[col * step];
+      SCAL[tid] = tid == 0 ? acc + jt[T] : acc;
     }
-    // the next chunk's first writes (TB, LT) are not read by thread 0 here,
+    // the next chunk's first writes (TB, LT) are not read by these threads here,
     // and its TRN2 writes follow two more barriers
   }
   __syncthreads();
@@ -668,6 +785,7 @@ __global__ __launch_bounds__(kThreads, WIDE ? 2 : 4) void k_lr_tangent(Dims d, D
   }
   if (tid == 0) {
     double dl = 0.0;
+#pragma unroll 8
     for (int p = 0; p < P; ++p) dl += WD[p] * DELTA[p];
     pw[0] = SCAL[0] + dl;
     pw[1] = SCAL[1];
@@ -724,10 +842,23 @@ void launch_lowrank_tangent(const pn_ctx* c, hipStream_t s, int64_t nw, char* ws
                        reinterpret_cast<const double*>(ws + L.wdet), flag, grad,
                        reinterpret_cast<double*>(ws + L.partial));
   };
-  if (std::max(d.n_up, d.n_dn) >= 8 && L.lds_lr > 40 * 1024)
-    go(&k_lr_tangent<true>);
+  const int n = std::max(d.n_up, d.n_dn);
+  auto pick = [&](auto kx_tag) {
+    constexpr int KX = decltype(kx_tag)::value;
+    if (n >= 8 && L.lds_lr > 40 * 1024)
+      n == 8 ? go(&k_lr_tangent<8, true, KX>) : go(&k_lr_tangent<0, true, KX>);
+    else if (n <= 4)
+      go(&k_lr_tangent<4, false, KX>);
+    else if (n <= 8)
+      n == 5 ? go(&k_lr_tangent<5, false, KX>) : n == 6 ? go(&k_lr_tangent<6, false, KX>)
+      : n == 7 ? go(&k_lr_tangent<7, false, KX>) : go(&k_lr_tangent<8, false, KX>);
+    else
+      go(&k_lr_tangent<0, false, KX>);
+  };
+  if (c->lr_kmax <= 2)
+    pick(std::integral_constant<int, 2>());
   else
-    go(&k_lr_tangent<false>);
+    pick(std::integral_constant<int, kMaxExc>());
   // the handed-back walkers: direct determinant tangents
   launch_slater_tangent(c, s, nw, nullptr, ws, L, grad, nullptr, list, list + nw);
 }

@@ -715,6 +715,7 @@ pn_status pn_ctx_create(const pn_system_desc* sys, const pn_net_desc* net, pn_ct
   t.pair_ij = dev_copy(pij, &err);
   t.pair_index = dev_copy(pidx, &err);
   t.lr_k = dev_copy(lrk, &err);
+  c->lr_kmax = lrk.empty() ? 0 : *std::max_element(lrk.begin(), lrk.end());
   t.lr_hole = dev_copy(lrh, &err);
   t.lr_part = dev_copy(lrp, &err);
   t.lr_sign = dev_copy(lrs, &err);

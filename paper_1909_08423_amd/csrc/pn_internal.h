@@ -182,6 +182,7 @@ struct pn_ctx {
     int64_t cnt[kStages] = {};
   };
   mutable Timing* timing = nullptr;
+  int lr_kmax = 0;  // most orbitals of a spin that a determinant replaces (low-rank path)
 };
 
 namespace pn {
