@@ -1,4 +1,5 @@
-// Network tangent pass, FP64 network; also the chunk planner helpers.
+// Network tangent pass, FP64 network, general widths; also the chunk planner
+// helpers and the choice of the width's form.
 #include "k_tangent_impl.h"
 
 namespace pn {
@@ -30,6 +31,37 @@ size_t tangent_lds_bytes(const Dims& d, int T, int stage) {
 
 template size_t tangent_lds_bytes<double>(const Dims&, int, int);
 template size_t tangent_lds_bytes<float>(const Dims&, int, int);
+template void launch_net_tangent_w<double, 0>(const pn_ctx*, hipStream_t, int64_t, const double*, const double*,
+                                              char*, const WsLayout&, bool, double*);
+
+// Widths with a form of their own (instantiated in their translation units).
+extern template void launch_net_tangent_w<float, 0>(const pn_ctx*, hipStream_t, int64_t, const double*, const float*,
+                                                    char*, const WsLayout&, bool, float*);
+#define PN_WIDTH(TN, SX)                                                                                       \
+  extern template void launch_net_tangent_w<TN, SX>(const pn_ctx*, hipStream_t, int64_t, const double*, const TN*, \
+                                                    char*, const WsLayout&, bool, TN*)
+PN_WIDTH(float, 32);
+PN_WIDTH(float, 64);
+PN_WIDTH(float, 128);
+PN_WIDTH(double, 32);
+PN_WIDTH(double, 64);
+PN_WIDTH(double, 128);
+#undef PN_WIDTH
+
+template <typename TN>
+void launch_net_tangent(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r, const TN* P, char* ws,
+                        const WsLayout& L, bool bf16, TN* xsave) {
+  auto go = [&](auto launch) { launch(c, s, nw, r, P, ws, L, bf16, xsave); };
+  const int sx = 2 * c->d.DZ == c->d.DX ? c->d.DX : 0;
+  switch (sx) {
+    case 32: go(&launch_net_tangent_w<TN, 32>); break;
+    case 64: go(&launch_net_tangent_w<TN, 64>); break;
+    case 128: go(&launch_net_tangent_w<TN, 128>); break;
+    default: go(&launch_net_tangent_w<TN, 0>); break;
+  }
+}
+template void launch_net_tangent<float>(const pn_ctx*, hipStream_t, int64_t, const double*, const float*, char*,
+                                        const WsLayout&, bool, float*);
 template void launch_net_tangent<double>(const pn_ctx*, hipStream_t, int64_t, const double*, const double*, char*,
                                          const WsLayout&, bool, double*);
 }  // namespace pn

@@ -1,0 +1,7 @@
+// Network tangent pass, F64 network, embedding width 128.
+#include "k_tangent_impl.h"
+
+namespace pn {
+template void launch_net_tangent_w<double, 128>(const pn_ctx*, hipStream_t, int64_t, const double*, const double*,
+                                            char*, const WsLayout&, bool, double*);
+}  // namespace pn
