@@ -1036,16 +1036,18 @@ void launch_c(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r, const
       return;
     }
   }
-  // Two 512-thread blocks per CU, four waves per SIMD, where a block leaves
-  // half the LDS and the kernel needs at most 128 registers: width 64 without
-  // row blocks (those hold 16 sums and their partial sums depend on the block
-  // size; width 32 gains nothing, width 128 leaves no LDS).  The kernel waits
-  // for LDS and caches half its time, and a channel's 300 to 450 message items
-  // are one round of 512 threads instead of two of 256.  Measured against 256
-  // threads: ten electrons FP32 2.82 -> 2.57 ms, BF16 6.55 -> 5.47, FP64 scan
-  // 1.76 -> 1.64, seven electrons (five evaluations) 9.35 -> 8.87.
-  if constexpr (SX == 64 && (C > 4 || STAGE) && C <= 11) {
-    if (L.lds_tangent <= 80 * 1024) {
+  // 512 threads, four waves per SIMD, where the LDS holds two blocks per CU
+  // and the kernel needs at most 128 registers: width 64 without row blocks
+  // (those hold 16 sums and their partial sums depend on the block size;
+  // width 32 gains nothing, width 128 leaves no LDS).  The kernel waits for
+  // LDS and caches half its time, and a channel's 300 to 450 message items are
+  // one round of 512 threads instead of two of 256.  Measured against 256
+  // threads, 4096 walkers: ten electrons FP32 2.82 -> 2.57 ms, 18 electrons
+  // 8.83 -> 7.70, eight FP64 3.84 -> 3.59; where three or more blocks of 256
+  // fit, the larger ones lose (six electrons FP32 1.29 -> 1.42 ms, three
+  // 0.52 -> 0.65).
+  if constexpr (SX == 64 && (C > 4 || STAGE)) {
+    if (L.lds_tangent > 160 * 1024 / 3 && L.lds_tangent <= 80 * 1024) {
       nt = 512;
       if constexpr (sizeof(TN) == sizeof(float)) {
         if (bf16) {
