@@ -507,12 +507,15 @@ __global__ __launch_bounds__(NT, WPE) void k_net_tangent(Dims d, DevTables t, in
               const TN ur = ua[al] * inv;
               const TN dw = -wd * ua[al];  // d/dr_k of w(|r_i - r_k|)
               const TN m = ok[al] ? TN(1) : TN(0);
-              // one rounding of this sum in FP32 chunks of ten coordinates, whose
-              // block sizes compile to different ones otherwise
-              if constexpr (C == 11 && sizeof(TN) == 4)
-                lap += m * fma(w2 * ur * ur + wd * (TN(1) - ur * ur), hk, TN(2) * dw * hc[al]);
+              // which of the two products is rounded on its own: fixed per
+              // chunk width, so that results do not depend on the block size
+              // (left to the compiler it does)
+              constexpr bool kRoundH = sizeof(TN) == 4 ? C == 11 : (C == 5 || C == 9);
+              const TN x2 = w2 * ur * ur + wd * (TN(1) - ur * ur);
+              if constexpr (kRoundH)
+                lap += m * fma(x2, hk, TN(2) * dw * hc[al]);
               else
-                lap += m * ((w2 * ur * ur + wd * (TN(1) - ur * ur)) * hk + TN(2) * dw * hc[al]);
+                lap += m * fma(TN(2) * dw, hc[al], x2 * hk);
               if (ok[al]) zi[cc[al] * LDZ] = zv[al] + dw * hk;
             }
           }
