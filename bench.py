@@ -96,7 +96,9 @@ def det_flops_per_walker(s, lowrank):
 
 
 # ------------------------------------------------------------- counters ----
-TANGENT_SOURCES = ["k_tangent_impl.h", "k_tangent_f32.hip", "k_tangent_f64.hip", "mfma_gemm.h", "gemm_lds.h"]
+TANGENT_SOURCES = ["k_tangent_impl.h", "k_tangent_f32.hip", "k_tangent_f32_w32.hip", "k_tangent_f32_w64.hip",
+                   "k_tangent_f32_w128.hip", "k_tangent_f64.hip", "k_tangent_f64_w32.hip", "k_tangent_f64_w64.hip",
+                   "k_tangent_f64_w128.hip", "mfma_gemm.h", "gemm_lds.h"]
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "k_net_tangent_cfg5_counters.md")
 
 
