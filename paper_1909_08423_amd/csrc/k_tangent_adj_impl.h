@@ -169,8 +169,8 @@ struct UnitsOfChunks {
 // Measured, all kernels of this file and the weight gradients: 86.4 -> 29 ms at
 // 256 walkers of the 30-electron diatomic (FP32), 12.7 -> 7.0 ms at 1024
 // walkers of a ten-atom chain (FP64).
-template <typename TN, int C, bool GA, int NT, int SX>
-__global__ __launch_bounds__(NT, 512 / NT) void k_tan_adj(
+template <typename TN, int C, bool GA, int NT, int SX, int WPE = 2>
+__global__ __launch_bounds__(NT, WPE) void k_tan_adj(
     Dims d, DevTables t, int n_chunks, const double* __restrict__ r, const TN* __restrict__ P, ParamLayout pl,
     const TN* __restrict__ filt, const TN* __restrict__ hval, const TN* __restrict__ kcoef,
     const TN* __restrict__ ecoef, const TN* __restrict__ xsave, const double* __restrict__ ctftan,
@@ -949,9 +949,17 @@ void launch_ta_c(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r, co
   const int64_t np = c->pl.total, batch = tan_batch<TN>(d, T, nw), NN = d.n_pairs;
   const bool ga = tan_adj_global<TN>(d, T);
   const size_t lds = tan_adj_small_lds<TN>(d, T) + (ga ? 0 : tan_adj_rows<TN>(d, T) * sizeof(TN));
-  // a block that takes more than half the CU's LDS runs alone on it
-  const int nt = lds > 80 * 1024 ? 512 : 256;
-  auto kern = ga ? (nt == 512 ? &k_tan_adj<TN, C, true, 512, SX> : &k_tan_adj<TN, C, true, 256, SX>)
+  // A block that takes more than half the CU's LDS runs alone on it, with 512
+  // threads.  Four waves per SIMD (two 512-thread blocks) where the LDS holds two blocks
+  // and 128 registers suffice, as in the tangent pass: full adjoints of 1024
+  // walkers of ten electrons FP64 11.85 -> 11.2 ms, 512 of 18 electrons FP32
+  // 9.5 -> 8.8.
+  constexpr bool kFour = SX == 64 && (sizeof(TN) == 4 || C <= 4);
+  constexpr int W = kFour ? 4 : 2;
+  const bool two = kFour && lds > 160 * 1024 / 3 && lds <= 80 * 1024;
+  const int nt = two || lds > 80 * 1024 ? 512 : 256;
+  auto kern = two  ? (ga ? &k_tan_adj<TN, C, true, 512, SX, W> : &k_tan_adj<TN, C, false, 512, SX, W>)
+              : ga ? (nt == 512 ? &k_tan_adj<TN, C, true, 512, SX> : &k_tan_adj<TN, C, true, 256, SX>)
                  : (nt == 512 ? &k_tan_adj<TN, C, false, 512, SX> : &k_tan_adj<TN, C, false, 256, SX>);
   if (lds > 65536)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
