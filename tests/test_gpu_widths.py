@@ -36,3 +36,20 @@ def test_widths(dx, dz, n):
         g = ctx.eval_backward(r, th, None, pn.PN_PREC_FP64, ct_lap=torch.tensor(ct, device="cuda")).cpu().numpy()
         gr = o.param_grad_full(w.walkers, ct_lap=ct).numpy()
         assert np.linalg.norm(g - gr) <= 1e-8 * np.linalg.norm(gr)
+
+
+@pytest.mark.parametrize("n", [10, 12])
+def test_full_adjoint_two_blocks_per_cu(n):
+    """Chunks of the full adjoint that leave LDS for two 512-thread blocks."""
+    announce(f"full adjoint, width 64, H{n}")
+    z = (np.arange(n) - (n - 1) / 2) * 1.8
+    xyz = np.stack([np.zeros(n), np.zeros(n), z], 1)
+    net = NetShape(16, 10.0, 64, 32, 2)
+    w = make_system_workload(f"H{n}", xyz, [1] * n, (n + 1) // 2, n // 2, [4] * n, [0] * n, 3, net, 2, 1.0, 5 * n)
+    ctx = pn.PauliNetContext(w.system, w.net)
+    r = torch.tensor(w.walkers, dtype=torch.float64, device="cuda")
+    th = torch.tensor(w.params, dtype=torch.float64, device="cuda")
+    ct = np.array([0.7, -1.3])
+    g = ctx.eval_backward(r, th, None, pn.PN_PREC_FP64, ct_lap=torch.tensor(ct, device="cuda")).cpu().numpy()
+    gr = Oracle(w.system, w.net, w.params).param_grad_full(w.walkers, ct_lap=ct).numpy()
+    assert np.linalg.norm(g - gr) <= 1e-8 * np.linalg.norm(gr)
