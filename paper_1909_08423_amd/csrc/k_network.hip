@@ -107,7 +107,11 @@ struct FOut {
 // bias and per activation and a block of 64 rows for every batch: 305 ->
 // 192 us at 4096 walkers of a ten-electron atom (FP32), 680 -> 469 us at 8192
 // walkers of a ten-atom chain (FP32), 46 -> 32 us at 512 walkers of H2 (FP64).
-template <typename TN>
+// ZCH: channels whose messages are in LDS together, 3, or 1 where a block of
+// one walker does not hold three message tables (from 43 electrons of widths
+// 128 / 64 in FP64): the channels then follow each other through one table,
+// with the same sums in the same order.
+template <typename TN, int ZCH>
 __global__ __launch_bounds__(kThreads, sizeof(TN) == 4 ? 3 : 2) void k_net_value(
     Dims d, DevTables t, int64_t nw, int WPB, const TN* __restrict__ P, ParamLayout pl, const TN* __restrict__ filt,
     TN* __restrict__ hval, TN* __restrict__ kcoef, TN* __restrict__ ecoef, double* __restrict__ fval,
@@ -122,8 +126,8 @@ __global__ __launch_bounds__(kThreads, sizeof(TN) == 4 ? 3 : 2) void k_net_value
   int* pidx = reinterpret_cast<int*>(smem);                  // [N][N]
   TN* X = reinterpret_cast<TN*>(pidx + ((N * N + 3) & ~3));  // [WPB*N][LDX]
   TN* H = X + WPB * N * LDX;                                 // [WPB*N][LDW] h, later the backflow head
-  TN* Z = H + WPB * N * LDW;                                 // [3][WPB*N][LDZ] messages
-  TN* E = Z + 3 * WPB * N * LDZ;                             // [2][WPB][LDX] Jastrow head
+  TN* Z = H + WPB * N * LDW;                                 // [ZCH][WPB*N][LDZ] messages
+  TN* E = Z + ZCH * WPB * N * LDZ;                           // [2][WPB][LDX] Jastrow head
   const int64_t fl_stride = (int64_t)3 * d.n_pairs * DZ;  // per layer
   const int64_t fw_stride = fl_stride * d.L;               // per walker
   const int ZS = WPB * N * LDZ;
@@ -146,49 +150,52 @@ __global__ __launch_bounds__(kThreads, sizeof(TN) == 4 ? 3 : 2) void k_net_value
                                    HOut<TN>{H, LDW, R, DZ, rN, P + Lp.hb, hval + (w0 * d.L + n) * N * DZ,
                                             (int64_t)d.L * N * DZ});
     __syncthreads();
-    for (int q = threadIdx.x; q < 3 * R * DZ; q += blockDim.x) {
-      const int q3 = q >> sz, ch = (q3 >= R) + (q3 >= 2 * R), row = q3 - ch * R, z = q & (DZ - 1);
-      const int wl = rN.div(row), i = row - wl * N;
-      const TN* fw = filt + (w0 + wl) * fw_stride + n * fl_stride + z;  // jet 0 = value
-      TN acc = 0;
-      if (ch < 2) {
-        // electrons of this channel: same spin (ch 0) or opposite spin
-        // (ch 1); j = i contributes w = 0
-        const bool want_up = (ch == 0) == (i < d.n_up);
-        const int j_lo = want_up ? 0 : d.n_up, j_hi = want_up ? d.n_up : N;
-        const TN* hw = H + wl * N * LDW + z;
-        for (int j = j_lo; j < j_hi; j += 8) {
-          TN wv[8], hv[8];
+    for (int ch0 = 0; ch0 < 3; ch0 += ZCH) {
+      for (int q = threadIdx.x; q < ZCH * R * DZ; q += blockDim.x) {
+        const int q3 = q >> sz, cz = ZCH == 1 ? 0 : (q3 >= R) + (q3 >= 2 * R), row = q3 - cz * R, z = q & (DZ - 1);
+        const int ch = ch0 + cz;
+        const int wl = rN.div(row), i = row - wl * N;
+        const TN* fw = filt + (w0 + wl) * fw_stride + n * fl_stride + z;  // jet 0 = value
+        TN acc = 0;
+        if (ch < 2) {
+          // electrons of this channel: same spin (ch 0) or opposite spin
+          // (ch 1); j = i contributes w = 0
+          const bool want_up = (ch == 0) == (i < d.n_up);
+          const int j_lo = want_up ? 0 : d.n_up, j_hi = want_up ? d.n_up : N;
+          const TN* hw = H + wl * N * LDW + z;
+          for (int j = j_lo; j < j_hi; j += 8) {
+            TN wv[8], hv[8];
 #pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const int jj = min(j + k, j_hi - 1);
-            wv[k] = fw[max(pidx[i * N + jj], 0) * DZ];
-            hv[k] = hw[jj * LDW];
+            for (int k = 0; k < 8; ++k) {
+              const int jj = min(j + k, j_hi - 1);
+              wv[k] = fw[max(pidx[i * N + jj], 0) * DZ];
+              hv[k] = hw[jj * LDW];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) acc += (j + k < j_hi && j + k != i) ? wv[k] * hv[k] : TN(0);
           }
-          __builtin_amdgcn_sched_barrier(0);
+        } else {
+          for (int I = 0; I < d.NN; I += 4) {
+            TN wv[4], yv[4];
 #pragma unroll
-          for (int k = 0; k < 8; ++k) acc += (j + k < j_hi && j + k != i) ? wv[k] * hv[k] : TN(0);
-        }
-      } else {
-        for (int I = 0; I < d.NN; I += 4) {
-          TN wv[4], yv[4];
+            for (int k = 0; k < 4; ++k) {
+              const int II = min(I + k, d.NN - 1);
+              wv[k] = fw[(d.n_ee + i * d.NN + II) * DZ];
+              yv[k] = P[pl.Y + II * DZ + z];
+            }
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const int II = min(I + k, d.NN - 1);
-            wv[k] = fw[(d.n_ee + i * d.NN + II) * DZ];
-            yv[k] = P[pl.Y + II * DZ + z];
+            for (int k = 0; k < 4; ++k) acc += I + k < d.NN ? wv[k] * yv[k] : TN(0);
           }
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int k = 0; k < 4; ++k) acc += I + k < d.NN ? wv[k] * yv[k] : TN(0);
         }
+        Z[cz * ZS + row * LDZ + z] = acc;
       }
-      Z[ch * ZS + row * LDZ + z] = acc;
+      __syncthreads();
+      for (int cz = 0; cz < ZCH; ++cz)
+        gemm_mfma<TN>(Z + cz * ZS, LDZ, R, DZ, P + Lp.gW[ch0 + cz], DX, X, LDX, true, false);
+      __syncthreads();
     }
-    __syncthreads();
-    for (int ch = 0; ch < 3; ++ch)
-      gemm_mfma<TN>(Z + ch * ZS, LDZ, R, DZ, P + Lp.gW[ch], DX, X, LDX, true, false);
-    __syncthreads();
     // the three channels' biases, added once
     for (int q = threadIdx.x; q < R * DX; q += blockDim.x) {
       const int x = q & (DX - 1);
@@ -253,25 +260,34 @@ __global__ __launch_bounds__(kThreads, sizeof(TN) == 4 ? 3 : 2) void k_net_value
 
 }  // namespace
 
+// LDS of the value pass: three message tables, or one where a single walker's
+// block does not hold them.
 template <typename TN>
-void launch_net_value(const pn_ctx* c, hipStream_t s, int64_t nw, const TN* P, char* ws, const WsLayout& L) {
-  const Dims& d = c->d;
-  int64_t nb = (nw + L.wpb_value - 1) / L.wpb_value;
-  if (L.lds_value > 65536)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_net_value<TN>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)L.lds_value);
-  hipLaunchKernelGGL(k_net_value<TN>, dim3((unsigned)nb), dim3(kThreads), L.lds_value, s, d, c->t, nw, L.wpb_value,
-                     P, c->pl, reinterpret_cast<const TN*>(ws + L.filt), reinterpret_cast<TN*>(ws + L.hval),
-                     reinterpret_cast<TN*>(ws + L.kcoef), reinterpret_cast<TN*>(ws + L.ecoef),
-                     reinterpret_cast<double*>(ws + L.fval), reinterpret_cast<double*>(ws + L.jval),
-                     L.xval ? reinterpret_cast<TN*>(ws + L.xval) : nullptr);
+static size_t value_lds_channels(const Dims& d, int wpb, int channels) {
+  const int LDX = ld_pad<TN>(d.DX), LDZ = ld_pad<TN>(d.DZ), LDW = std::max(LDX, LDZ);
+  return (size_t)((d.N * d.N + 3) & ~3) * sizeof(int) +
+         ((size_t)wpb * d.N * (LDX + LDW + channels * LDZ) + 2 * (size_t)wpb * LDX) * sizeof(TN);
 }
 
 template <typename TN>
 size_t value_lds_bytes(const Dims& d, int wpb) {
-  const int LDX = ld_pad<TN>(d.DX), LDZ = ld_pad<TN>(d.DZ), LDW = std::max(LDX, LDZ);
-  return (size_t)((d.N * d.N + 3) & ~3) * sizeof(int) +
-         ((size_t)wpb * d.N * (LDX + LDW + 3 * LDZ) + 2 * (size_t)wpb * LDX) * sizeof(TN);
+  const size_t three = value_lds_channels<TN>(d, wpb, 3);
+  return wpb > 1 || three <= 160 * 1024 ? three : value_lds_channels<TN>(d, wpb, 1);
+}
+
+template <typename TN>
+void launch_net_value(const pn_ctx* c, hipStream_t s, int64_t nw, const TN* P, char* ws, const WsLayout& L) {
+  const Dims& d = c->d;
+  int64_t nb = (nw + L.wpb_value - 1) / L.wpb_value;
+  auto kern = L.lds_value == value_lds_channels<TN>(d, L.wpb_value, 3) ? &k_net_value<TN, 3> : &k_net_value<TN, 1>;
+  if (L.lds_value > 65536)
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)L.lds_value);
+  hipLaunchKernelGGL(kern, dim3((unsigned)nb), dim3(kThreads), L.lds_value, s, d, c->t, nw, L.wpb_value,
+                     P, c->pl, reinterpret_cast<const TN*>(ws + L.filt), reinterpret_cast<TN*>(ws + L.hval),
+                     reinterpret_cast<TN*>(ws + L.kcoef), reinterpret_cast<TN*>(ws + L.ecoef),
+                     reinterpret_cast<double*>(ws + L.fval), reinterpret_cast<double*>(ws + L.jval),
+                     L.xval ? reinterpret_cast<TN*>(ws + L.xval) : nullptr);
 }
 
 template void launch_net_value<double>(const pn_ctx*, hipStream_t, int64_t, const double*, char*, const WsLayout&);

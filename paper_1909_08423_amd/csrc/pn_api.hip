@@ -354,6 +354,15 @@ WsLayout plan(const pn_ctx* c, int64_t nw, pn_precision prec, int mode, size_t b
   return L;
 }
 
+// Neither head: psi does not depend on the network, which no kernel evaluates.
+static bool no_network(const Dims& d) {
+  return (d.flags & (PN_NET_NO_JASTROW | PN_NET_NO_BACKFLOW)) == (PN_NET_NO_JASTROW | PN_NET_NO_BACKFLOW);
+}
+
+// The value pass of this plan fits a workgroup's LDS (every call that runs it
+// asks before it enqueues anything).
+static bool value_pass_fits(const Dims& d, const WsLayout& L) { return no_network(d) || L.lds_value <= kLdsMax; }
+
 // ---- optional stage timing ----
 namespace {
 void harvest_set(pn_ctx::Timing* T, int set) {
@@ -849,7 +858,7 @@ pn_status pn_eval(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r, c
   if (!r || !params || !logabs || !sign || !ws) return PN_ERR_INVALID_ARG;
   WsLayout L = plan(c, nw, prec, (grad || lap || eloc) ? kPlanForward : kPlanValueOnly);
   if (ws_bytes < L.total) return PN_ERR_WORKSPACE_TOO_SMALL;
-  if (L.lds_tangent > kLdsMax) return PN_ERR_UNSUPPORTED_SHAPE;
+  if (L.lds_tangent > kLdsMax || !value_pass_fits(c->d, L)) return PN_ERR_UNSUPPORTED_SHAPE;
   return eval_impl(c, s, nw, r, params, prec, logabs, sign, grad, lap, eloc, static_cast<char*>(ws), L);
 }
 
@@ -863,7 +872,7 @@ pn_status pn_eval_noalloc(const pn_ctx* c, hipStream_t s, int64_t nw, const doub
   // walker tiles sized for the static scratch (down to one walker)
   WsLayout L = plan(c, nw, prec, (grad || lap || eloc) ? kPlanForward : kPlanValueOnly, kScratchBytes, 1);
   if (L.total > kScratchBytes) return PN_ERR_WORKSPACE_TOO_SMALL;
-  if (L.lds_tangent > kLdsMax) return PN_ERR_UNSUPPORTED_SHAPE;
+  if (L.lds_tangent > kLdsMax || !value_pass_fits(c->d, L)) return PN_ERR_UNSUPPORTED_SHAPE;
   return eval_impl(c, s, nw, r, params, prec, logabs, sign, grad, lap, eloc, base, L);
 }
 
@@ -879,7 +888,7 @@ pn_status eval_impl(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r,
   const bool fp64 = prec == PN_PREC_FP64, bf16 = prec == PN_PREC_NET_BF16;
   const bool derivs = grad || lap || eloc;
   const Dims& d = c->d;
-  const bool no_net = (d.flags & (PN_NET_NO_JASTROW | PN_NET_NO_BACKFLOW)) == (PN_NET_NO_JASTROW | PN_NET_NO_BACKFLOW);
+  const bool no_net = no_network(d);
   const void* P = params;
   StageClock clk(c, s);
   if (!fp64) {
@@ -958,13 +967,13 @@ pn_status pn_eval_backward(const pn_ctx* c, hipStream_t s, int64_t nw, const dou
   if (!r || !params || !grad_params || !ws) return PN_ERR_INVALID_ARG;
   const bool full = ct_grad || ct_lap || ct_eloc;
   if (!full && !ct_logabs) return PN_OK;  // every cotangent is zero
-  if ((c->d.flags & (PN_NET_NO_JASTROW | PN_NET_NO_BACKFLOW)) == (PN_NET_NO_JASTROW | PN_NET_NO_BACKFLOW))
-    return PN_OK;  // without both heads psi does not depend on the parameters
+  if (no_network(c->d)) return PN_OK;  // without both heads psi does not depend on the parameters
   const bool fp64 = prec == PN_PREC_FP64, bf16 = prec == PN_PREC_NET_BF16;
   if (!backward_supported(c, !fp64)) return PN_ERR_UNSUPPORTED_SHAPE;
   WsLayout L = plan(c, nw, prec, full ? kPlanFullAdjoint : kPlanValueAdjoint);
   if (ws_bytes < L.total) return PN_ERR_WORKSPACE_TOO_SMALL;
   const Dims& d = c->d;
+  if (!value_pass_fits(d, L)) return PN_ERR_UNSUPPORTED_SHAPE;
   if (full && (L.lds_tadj > kLdsMax || L.lds_adjdet > kLdsMax || L.lds_tangent > kLdsMax ||
                backward_filter_lds_bytes(d, !fp64, true) > kLdsMax))
     return PN_ERR_UNSUPPORTED_SHAPE;
@@ -1031,13 +1040,14 @@ pn_status pn_eval_backward_cusp(const pn_ctx* c, hipStream_t s, int64_t nw, cons
   const bool fp64 = prec == PN_PREC_FP64;
   WsLayout L = plan(c, nw, prec, kPlanValueAdjoint);
   if (ws_bytes < L.total) return PN_ERR_WORKSPACE_TOO_SMALL;
+  if (!value_pass_fits(d, L)) return PN_ERR_UNSUPPORTED_SHAPE;
   char* base = static_cast<char*>(ws);
   const void* P = params;
   if (!fp64) {
     launch_convert_params(s, c->pl.total, params, reinterpret_cast<float*>(base + L.params_net));
     P = base + L.params_net;
   }
-  const bool no_net = (d.flags & (PN_NET_NO_JASTROW | PN_NET_NO_BACKFLOW)) == (PN_NET_NO_JASTROW | PN_NET_NO_BACKFLOW);
+  const bool no_net = no_network(d);
   double* la = reinterpret_cast<double*>(base + L.adj);
   double* sg = la + L.tile;
   double* slot = reinterpret_cast<double*>(base + L.gpart);  // per-block partial sums

@@ -1,0 +1,72 @@
+"""Every call either launches only what the hardware takes or is refused
+before anything is enqueued, over the sizes the library accepts (no GPU: the
+launches are recorded by a stand-in for the HIP runtime)."""
+
+import itertools
+import json
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+import paper_1909_08423_amd as pn
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LDS = 160 * 1024
+FP64, FP32 = pn.PN_PREC_FP64, pn.PN_PREC_NET_FP32
+OK, UNSUPPORTED = 0, 2
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    if not os.path.exists(pn.library_path()):
+        pytest.skip("library not built")
+    cc = shutil.which("gcc") or shutil.which("cc")
+    if cc is None:
+        pytest.skip("no C compiler")
+    so = str(tmp_path_factory.mktemp("fake") / "fake_hip.so")
+    subprocess.run([cc, "-shared", "-fPIC", "-O1", "-o", so, os.path.join(HERE, "fake_hip.c")], check=True)
+
+    def go(calls):
+        r = subprocess.run([sys.executable, os.path.join(HERE, "host_launches.py"), so], input=json.dumps(calls),
+                           capture_output=True, text=True, check=True)
+        return json.loads(r.stdout)
+
+    return go
+
+
+def widths():
+    return itertools.product((16, 32, 64, 128), (16, 32, 64, 128))
+
+
+def pad(d, size):
+    return d + 16 // size
+
+
+def wide_tables(n, dx, dz, size):
+    """LDS of a value-pass block with one message table of the wider width:
+    what the value pass asks of a system at least."""
+    ldx, ldw = pad(dx, size), pad(max(dx, dz), size)
+    return ((n * n + 3) & ~3) * 4 + (n * (ldx + 2 * ldw) + 2 * ldx) * size
+
+
+@pytest.mark.parametrize("kind", ["adjoint", "cusp"])
+def test_value_pass_sizes(run, kind):
+    calls, fits = [], []
+    for n in range(1, 65):
+        for dx, dz in widths():
+            up, down = (n + 1) // 2, n // 2
+            if up > dx:
+                continue
+            for prec, size in ((FP64, 8), (FP32, 4)):
+                calls.append([[up, down, 2, min(dx, up + 2), 2], [16, dx, dz, 2, 0], 8, prec, kind])
+                # the adjoint's filter gradients exist for D_z up to 64 here
+                fits.append(wide_tables(n, dx, dz, size) <= LDS and (kind == "cusp" or dz <= 64))
+    for call, fit, (status, launches, beyond) in zip(calls, fits, run(calls)):
+        assert not beyond, (call, beyond[0])
+        if fit:
+            assert status == OK and launches > 0, call
+        else:
+            assert status == OK or (status == UNSUPPORTED and launches == 0), call
