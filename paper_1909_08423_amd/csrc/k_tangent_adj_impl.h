@@ -760,14 +760,16 @@ __global__ __launch_bounds__(256) void k_tan_ww(Dims d, DevTables t, int n_chunk
   }
 }
 
-// The other value-pass cotangents: one thread per element, chunks in order.
+// The other value-pass cotangents: one thread per element, chunks in order;
+// bpw blocks per walker (a batch of a small system has more walkers than a
+// grid has blocks in y).
 template <typename TN>
-__global__ __launch_bounds__(kThreads) void k_tan_sum(Dims d, int n_chunks, int T, const TN* __restrict__ ops,
+__global__ __launch_bounds__(kThreads) void k_tan_sum(Dims d, int n_chunks, int T, int bpw, const TN* __restrict__ ops,
                                                       TanOps to, TanAdjOut<TN> out) {
-  const int64_t w = blockIdx.y;
+  const int64_t w = blockIdx.x / (unsigned)bpw;
   const int N = d.N, DX = d.DX, DZ = d.DZ, L = d.L, NN = d.NN, NP = N + NN, N3 = 3 * N;
   const int n_hv = L * N * DZ, n_pw = L * d.n_pairs * DZ, n_kc = 4 * N * DX, n_ec = 4 * DX, n_w0 = d.n_ee * DZ;
-  int q = blockIdx.x * blockDim.x + threadIdx.x;
+  int q = (int)(blockIdx.x % (unsigned)bpw) * blockDim.x + threadIdx.x;
   const TN* base = ops + w * n_chunks * to.len;
   auto sum = [&](int64_t at) {
     TN v = 0;
@@ -1017,8 +1019,8 @@ void launch_ta_c(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r, co
                          lds_ww, s, d, c->t, nch, ops, to, o.ww);
     const int64_t elems = (int64_t)d.L * d.N * d.DZ + 4 * d.N * d.DX + 4 * d.DX + d.n_ee * d.DZ +
                           (int64_t)d.L * d.n_pairs * d.DZ;
-    hipLaunchKernelGGL(k_tan_sum<TN>, dim3((unsigned)((elems + kThreads - 1) / kThreads), (unsigned)n), dim3(kThreads), 0,
-                       s, d, nch, T, ops, to, o);
+    const int bpw = (int)((elems + kThreads - 1) / kThreads);
+    hipLaunchKernelGGL(k_tan_sum<TN>, dim3((unsigned)(n * bpw)), dim3(kThreads), 0, s, d, nch, T, bpw, ops, to, o);
   }
 }
 

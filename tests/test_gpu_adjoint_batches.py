@@ -1,0 +1,37 @@
+"""The full adjoint takes its walkers in batches of 2 GiB of tables; a batch
+may hold more walkers than a grid has blocks in y."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_1909_08423_amd as pn
+from synth.configs import NetShape, make_system_workload
+
+pytestmark = pytest.mark.gpu
+
+
+def whole_and_parts(w, cut):
+    print(w.name, len(w.walkers), cut, flush=True)
+    n = len(w.walkers)
+    ctx = pn.PauliNetContext(w.system, w.net)
+    rng = np.random.default_rng(n)
+    r = torch.tensor(w.walkers, dtype=torch.float64, device="cuda")
+    th = torch.tensor(w.params, dtype=torch.float64, device="cuda")
+    cg = torch.tensor(rng.standard_normal(w.walkers.shape), device="cuda")
+    cl = torch.tensor(rng.standard_normal(n), device="cuda")
+
+    def grad(a, b):
+        return ctx.eval_backward(r[a:b], th, None, pn.PN_PREC_FP64, ct_grad=cg[a:b], ct_lap=cl[a:b])
+
+    whole = grad(0, n)
+    parts = sum(grad(a, b) for a, b in zip([0] + cut, cut + [n]))
+    return ctx, whole, parts
+
+
+def test_more_walkers_than_blocks_in_y():
+    net = NetShape(16, 10.0, 16, 16, 1)
+    w = make_system_workload("H", [[0.0, 0.0, 0.0]], [1], 1, 0, [4], [0], 2, net, 70001, 1.0, 11)
+    ctx, whole, parts = whole_and_parts(w, [35000])
+    # few parameters have a gradient of their own at one electron: against the whole
+    assert torch.linalg.norm(whole - parts) <= 1e-10 * torch.linalg.norm(whole)

@@ -70,3 +70,13 @@ def test_value_pass_sizes(run, kind):
             assert status == OK and launches > 0, call
         else:
             assert status == OK or (status == UNSUPPORTED and launches == 0), call
+
+
+def test_full_adjoint_of_many_walkers(run):
+    """Batches of small systems have more walkers than a grid has blocks in y."""
+    calls = [[sys, net, nw, prec, "full"]
+             for sys, net in (([1, 0, 1, 1, 1], [16, 16, 16, 1, 0]), ([1, 1, 2, 4, 2], [16, 16, 16, 1, 0]),
+                              ([2, 0, 5, 6, 8], [64, 16, 32, 1, 0]), ([1, 1, 1, 4, 2], [16, 32, 16, 2, 0]))
+             for nw in (65536, 65537, 300000) for prec in (FP64, FP32)]
+    for call, (status, launches, beyond) in zip(calls, run(calls)):
+        assert status == OK and launches > 0 and not beyond, (call, beyond)
