@@ -1,12 +1,14 @@
-"""The full adjoint takes its walkers in batches of 2 GiB of tables; a batch
-may hold more walkers than a grid has blocks in y."""
+"""The full adjoint takes its walkers in batches of 2 GiB of tables: a
+gradient over several batches equals the sum of its parts, the filter
+parameters (which the batches' pair cotangents reach) included, and a batch may
+hold more walkers than a grid has blocks in y."""
 
 import numpy as np
 import pytest
 import torch
 
 import paper_1909_08423_amd as pn
-from synth.configs import NetShape, make_system_workload
+from synth.configs import NetShape, make_config, make_system_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -27,6 +29,24 @@ def whole_and_parts(w, cut):
     whole = grad(0, n)
     parts = sum(grad(a, b) for a, b in zip([0] + cut, cut + [n]))
     return ctx, whole, parts
+
+
+def check(ctx, whole, parts):
+    # the same walkers' terms in another order of FP64 sums
+    for name, off, shape in ctx.param_layout():
+        k = slice(off, off + int(np.prod(shape)))
+        assert torch.linalg.norm((whole - parts)[k]) <= 1e-10 * torch.linalg.norm(whole[k]), name
+
+
+def test_parameters_over_several_batches():
+    w = make_config(5, n_walkers=70)
+    ctx, whole, parts = whole_and_parts(w, [15, 30, 45, 60])
+    plan = ctx.plan(70, pn.PN_PREC_FP64, 2)  # full adjoint
+    rows = w.system.n_elec * (plan["chunk_coords"] + 1)
+    net = w.net  # a chunk's activations and cotangents of the backflow head and the layers, at least
+    table = plan["n_chunks"] * rows * (4 * net.dim_x + net.n_layers * (net.dim_x + 2 * net.dim_z)) * 8
+    assert 70 * table > 2 * 2**31, "two batches and a part at least"
+    check(ctx, whole, parts)
 
 
 def test_more_walkers_than_blocks_in_y():
