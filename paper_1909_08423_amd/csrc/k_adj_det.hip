@@ -42,6 +42,13 @@
 namespace pn {
 namespace {
 
+// orders a wave's LDS accesses before and after it, across lanes
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ double wave_sum_d(double v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
@@ -348,6 +355,7 @@ __global__ __launch_bounds__(128) void k_adj_slater_16(Dims d, DevTables t, int 
       for (int v = 0; v < 4; ++v) q[v] += fma(2.0 * cD, m2[v], -ca * mt[v]);
     }
     const v4d cA = mfma16(gA, q, z);  // (Q G)^T
+    wave_sync();  // an orbital's slot, and with it its lane, changes from member to member
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       if (mu[v] < 0) continue;
