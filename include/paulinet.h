@@ -193,7 +193,8 @@ pn_status pn_workspace_bytes(const pn_ctx* ctx, int64_t n_walkers, pn_precision 
 /* Workspace bytes that also cover pn_eval_backward with cotangents on the
  * gradient, Laplacian or local energy (the full adjoint keeps the layer
  * inputs of the tangent pass and per-chunk cotangent tables per walker
- * tile); never less than pn_workspace_bytes. */
+ * tile, and the tables of one batch of its walkers, up to 2 GiB or one
+ * walker's); never less than pn_workspace_bytes. */
 pn_status pn_workspace_bytes_full(const pn_ctx* ctx, int64_t n_walkers, pn_precision prec, size_t* bytes);
 
 /* How a call with n_walkers walkers is carried out: walkers per internal

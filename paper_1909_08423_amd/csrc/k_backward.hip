@@ -33,8 +33,8 @@
 namespace pn {
 namespace {
 
-constexpr int kSlotsNet = 512;     // gradient slots of the network weights
-constexpr int kSlotsFilter = 256;  // blocks per (layer, channel) of k_bwd_filter
+constexpr int kSlotsNet = 512;     // gradient slots of the network weights, at most
+constexpr int kSlotsFilter = 256;  // blocks per (layer, channel) of k_bwd_filter, at most
 constexpr int kFiltRows = 32;      // (walker, pair) rows per tile of k_bwd_filter, at most
 
 // What k_bwd_net leaves behind for the weight gradients ([walker][row]
@@ -87,8 +87,9 @@ __device__ __forceinline__ void colsum(const TN* Y, int ldy, int B, int rows, TN
 template <typename TN, int NT>
 __global__ __launch_bounds__(NT, 512 / NT) void k_bwd_net(Dims d, DevTables t, int64_t nw, int WB,
                                                           const TN* __restrict__ P, ParamLayout pl,
-                                                          const TN* __restrict__ xval, const TN* __restrict__ hval,
-                                                          const TN* __restrict__ filt, const double* __restrict__ phi,
+                                                          const TN* __restrict__ xval, const TN* hval,
+                                                          int jets, const TN* __restrict__ filt,
+                                                          const double* __restrict__ phi,
                                                           const double* __restrict__ ginv,
                                                           const double* __restrict__ wdet,
                                                           const double* __restrict__ ct_logabs, TN* __restrict__ ctw,
@@ -126,7 +127,8 @@ __global__ __launch_bounds__(NT, 512 / NT) void k_bwd_net(Dims d, DevTables t, i
   TN* H = UN;                  // [RW][LDZ]
   TN* CZ = H + RW * LDZ;       // [3][RW][LDZ]
   TN* CH = CZ + 3 * RW * LDZ;  // [RW][LDZ]
-  const int64_t fl_stride = (int64_t)3 * d.n_pairs * DZ;
+  const int64_t fl_stride = (int64_t)jets * d.n_pairs * DZ;
+  const int64_t h_walker = jets == 1 ? 1 : L, h_layer = jets == 1 ? nw : 1;  // h table, in units of a walker's layer
   const int64_t ng = (nw + WB - 1) / WB;
   const int n_same = (d.n_up * (d.n_up - 1) + d.n_dn * (d.n_dn - 1)) / 2;
   const TN jas = (d.flags & PN_NET_NO_JASTROW) ? TN(0) : TN(1);  // a removed Jastrow factor gets no cotangent
@@ -320,10 +322,9 @@ __global__ __launch_bounds__(NT, 512 / NT) void k_bwd_net(Dims d, DevTables t, i
       TN* sml = small + sm.layer + n * sm.step;
       for (int q = threadIdx.x; q < R * DZ; q += blockDim.x) {
         const int row = q >> sz, z = q & (DZ - 1), wl = rN.div(row);
-        const int64_t o = (((w0 + wl) * L + n) * N + (row - wl * N)) * DZ + z;
-        H[row * LDZ + z] = hval[o];
+        H[row * LDZ + z] = hval[(((w0 + wl) * h_walker + n * h_layer) * N + (row - wl * N)) * DZ + z];
         // the tangent pass's cotangent of the h values seeds the h adjoint
-        CH[row * LDZ + z] = cthv ? cthv[o] : TN(0);
+        CH[row * LDZ + z] = cthv ? cthv[(((w0 + wl) * L + n) * N + (row - wl * N)) * DZ + z] : TN(0);
       }
       {
         TN* oc = op.cx + ((int64_t)n * nw * N + row0) * DX;
@@ -868,24 +869,29 @@ static int bwd_filter_rows(const Dims& d, bool fp32, bool full) {
 
 static size_t filt_fsz(const Dims& d) { return (size_t)d.K * d.DZ + d.DZ + (size_t)d.DZ * d.DZ + d.DZ; }
 
-// elements of the row tables that k_bwd_net leaves for the weight gradients
-static size_t net_ops_elems(const Dims& d, int64_t nw) {
-  const size_t rows = (size_t)nw * d.N;
-  return (size_t)d.L * rows * (4 * (size_t)d.DZ + d.DX) + rows * (4 * (size_t)d.DX + d.M) + 4 * (size_t)nw * d.DX;
+// gradient slots in use: one per group of walkers, one per block of filter rows
+static int64_t net_slots(int64_t nw, int wb) { return std::min<int64_t>((nw + wb - 1) / wb, kSlotsNet); }
+static int64_t filter_slots(const Dims& d, int64_t nw, int pt) {
+  const int n_same = d.n_up * (d.n_up - 1) / 2 + d.n_dn * (d.n_dn - 1) / 2;
+  const int64_t max_np = std::max<int64_t>(std::max(n_same, d.n_ee - n_same), (int64_t)d.N * d.NN);
+  return std::min<int64_t>((nw * max_np + pt - 1) / pt, kSlotsFilter);
 }
 
-size_t backward_scratch_bytes(const pn_ctx* c, int64_t tile, bool fp32) {
+// Scratch of a tile.  The row tables for the weight gradients are here as far
+// as no region of the value pass that is read no more holds them (run_backward).
+size_t backward_scratch_bytes(const pn_ctx* c, int64_t tile, bool fp32, bool full) {
   const Dims& d = c->d;
   const size_t tn = fp32 ? sizeof(float) : sizeof(double);
-  size_t b = 0;
-  b += (size_t)kSlotsNet * c->pl.total * tn;                       // net slots
-  b += (size_t)kSlotsFilter * d.L * 3 * filt_fsz(d) * tn;          // filter slots
-  b += (size_t)tile * d.L * d.n_pairs * d.DZ * tn;                 // filter cotangents
   const bool arena = fp32 ? bwd_net_arena<float>(d) : bwd_net_arena<double>(d);
   const int wb = fp32 ? bwd_wb<float>(d) : bwd_wb<double>(d);
-  if (arena) b += (size_t)kSlotsNet * (fp32 ? bwd_net_union<float>(d, wb) : bwd_net_union<double>(d, wb)) * tn;
-  b += (net_ops_elems(d, tile) + (size_t)((tile + wb - 1) / wb) * SmallSums(d).total) * tn;
-  return b + 32 * 256;
+  const size_t slots = net_slots(tile, wb), groups = (tile + wb - 1) / wb;
+  size_t e = slots * c->pl.total;                                                          // net slots
+  e += filter_slots(d, tile, bwd_filter_rows(d, fp32, full)) * d.L * 3 * filt_fsz(d);       // filter slots
+  e += (size_t)tile * d.L * d.n_pairs * d.DZ;                                               // filter cotangents
+  if (arena) e += slots * (fp32 ? bwd_net_union<float>(d, wb) : bwd_net_union<double>(d, wb));
+  e += (size_t)d.L * tile * d.N * ((full ? 4 : 3) * (size_t)d.DZ + d.DX);                   // row tables
+  e += groups * SmallSums(d).total;                                                         // group sums
+  return e * tn + 8 * 256;
 }
 
 bool backward_supported(const pn_ctx* c, bool fp32) {
@@ -901,10 +907,10 @@ static void run_backward(const pn_ctx* c, hipStream_t s, int64_t nw, const doubl
                          char* ws, const WsLayout& L, double* grad, bool full) {
   const Dims& d = c->d;
   const int64_t np = c->pl.total;
+  const int WB = bwd_wb<TN>(d), PT = bwd_filter_rows(d, sizeof(TN) == sizeof(float), full);
   TN* gslot = reinterpret_cast<TN*>(ws + L.gpart);
-  TN* fslot = gslot + (size_t)kSlotsNet * np;
-  TN* ctw = fslot + (size_t)kSlotsFilter * d.L * 3 * filt_fsz(d);
-  const int WB = bwd_wb<TN>(d);
+  TN* fslot = gslot + net_slots(L.tile, WB) * np;
+  TN* ctw = fslot + filter_slots(d, L.tile, PT) * d.L * 3 * filt_fsz(d);
   const int64_t ng = (nw + WB - 1) / WB;
   const int64_t rows = nw * d.N;
   const SmallSums sm(d);
@@ -918,20 +924,24 @@ static void run_backward(const pn_ctx* c, hipStream_t s, int64_t nw, const doubl
   };
   const bool use_arena = bwd_net_arena<TN>(d);
   const int64_t arena_elems = use_arena ? (int64_t)bwd_net_union<TN>(d, WB) : 0;
-  TN* arena = use_arena ? take((size_t)kSlotsNet * arena_elems) : nullptr;
+  TN* arena = use_arena ? take(net_slots(L.tile, WB) * arena_elems) : nullptr;
+  // row tables take the place of what only the value pass and the tangent
+  // kernels before this one read: the heads' slopes (as many tables of the same
+  // size) and the backflow; without tangents also that of h, which a block
+  // reads before it writes the cotangent there
   NetOps<TN> op;
   op.z = take((size_t)d.L * 3 * rows * d.DZ);
   op.cx = take((size_t)d.L * rows * d.DX);
-  op.ch = take((size_t)d.L * rows * d.DZ);
-  op.a1 = take((size_t)rows * d.DX);
-  op.c2 = take((size_t)rows * d.DX);
-  op.c1 = take((size_t)rows * d.DX);
-  op.a2 = take((size_t)rows * d.DX);
-  op.cf = take((size_t)rows * d.M);
-  op.s = take((size_t)nw * d.DX);
-  op.e1 = take((size_t)nw * d.DX);
-  op.ec1 = take((size_t)nw * d.DX);
-  op.ec2 = take((size_t)nw * d.DX);
+  op.ch = full ? take((size_t)d.L * rows * d.DZ) : reinterpret_cast<TN*>(ws + L.hval);
+  op.a1 = reinterpret_cast<TN*>(ws + L.kcoef);
+  op.c2 = op.a1 + rows * d.DX;
+  op.c1 = op.c2 + rows * d.DX;
+  op.a2 = op.c1 + rows * d.DX;
+  op.cf = reinterpret_cast<TN*>(ws + L.fval);
+  op.s = reinterpret_cast<TN*>(ws + L.ecoef);
+  op.e1 = op.s + nw * d.DX;
+  op.ec1 = op.e1 + nw * d.DX;
+  op.ec2 = op.ec1 + nw * d.DX;
   op.small = take((size_t)ng * sm.total);
   const TN* xval = reinterpret_cast<const TN*>(ws + L.xval);
   const size_t lds = bwd_net_lds<TN>(d, WB, use_arena);
@@ -941,9 +951,9 @@ static void run_backward(const pn_ctx* c, hipStream_t s, int64_t nw, const doubl
   if (lds > 65536)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(net_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds);
-  const int nb_net = (int)std::min<int64_t>(ng, kSlotsNet);
+  const int nb_net = (int)net_slots(nw, WB);
   hipLaunchKernelGGL(net_kernel, dim3((unsigned)(use_arena ? nb_net : ng)), dim3(nt), lds, s, d, c->t, nw, WB, P, c->pl,
-                     xval, reinterpret_cast<const TN*>(ws + L.hval), reinterpret_cast<const TN*>(ws + L.filt),
+                     xval, reinterpret_cast<const TN*>(ws + L.hval), L.jets, reinterpret_cast<const TN*>(ws + L.filt),
                      reinterpret_cast<const double*>(ws + L.phi), reinterpret_cast<const double*>(ws + L.ginv),
                      reinterpret_cast<const double*>(ws + L.wdet), ct, ctw,
                      full ? reinterpret_cast<const double*>(ws + L.ctfpart) : nullptr, L.n_chunks,
@@ -970,9 +980,7 @@ static void run_backward(const pn_ctx* c, hipStream_t s, int64_t nw, const doubl
   hipLaunchKernelGGL(k_wgrad_small<TN>, dim3((unsigned)((d.DX * d.M + sm.total + kThreads - 1) / kThreads), nb_net),
                      dim3(kThreads), 0, s, d, c->pl, units, op.a2, op.cf, op.small, gslot, np);
   const int n_same = d.n_up * (d.n_up - 1) / 2 + d.n_dn * (d.n_dn - 1) / 2;
-  const int64_t max_np = std::max<int64_t>(std::max(n_same, d.n_ee - n_same), (int64_t)d.N * d.NN);
-  const int PT = bwd_filter_rows(d, sizeof(TN) == sizeof(float), full);
-  const int nb_f = (int)std::min<int64_t>((nw * max_np + PT - 1) / PT, kSlotsFilter);
+  const int nb_f = (int)filter_slots(d, nw, PT);
   const size_t lds_f = bwd_filter_lds<TN>(d, PT, full);
   auto go = [&](auto kern, int nt) {
     if (lds_f > 65536)

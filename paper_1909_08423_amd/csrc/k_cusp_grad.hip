@@ -86,6 +86,10 @@ __global__ __launch_bounds__(kThreads) void k_cusp_reduce(int n, int nslots, con
 
 }  // namespace
 
+size_t cusp_grad_slot_bytes(const Dims& d, int64_t nw) {
+  return (size_t)std::min<int64_t>(nw, kSlotsCusp) * d.NN * d.M * sizeof(double);
+}
+
 size_t cusp_grad_lds_bytes(const Dims& d) { return (size_t)d.N * d.NN * d.M * sizeof(double); }
 
 void launch_cusp_grad(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r, char* ws, const WsLayout& L,

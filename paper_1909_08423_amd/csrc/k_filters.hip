@@ -63,7 +63,7 @@ __global__ __launch_bounds__(kThreads) void k_filters(Dims d, DevTables t, int64
   int64_t* doff = reinterpret_cast<int64_t*>(dd + PT);  // [PT] table offset of each row (layer 0)
   TN* E = reinterpret_cast<TN*>(doff + PT);           // [NJ][PT][LDK] feature jets
   TN* U = E + NJ * PT * LDK;                          // [NJ][PT][LDZ] ssp jets
-  const int64_t lstride = (int64_t)3 * d.n_pairs * DZ, jstride = (int64_t)d.n_pairs * DZ;
+  const int64_t lstride = (int64_t)NJ * d.n_pairs * DZ, jstride = (int64_t)d.n_pairs * DZ;
 
   // --- distances (padding rows of a partial tile: 0) ---
   for (int q = threadIdx.x; q < PT; q += blockDim.x) {
@@ -212,8 +212,9 @@ template size_t filter_lds_bytes<float>(const Dims&, int, bool);
 
 template <typename TN>
 void launch_filters(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r, const TN* P, char* ws,
-                    const WsLayout& L, bool jets) {
+                    const WsLayout& L) {
   const Dims& d = c->d;
+  const bool jets = L.jets == 3;
   const int PT = L.filt_rows;
   int n_same = 0;
   // same-spin ee pairs: n_up(n_up-1)/2 + n_dn(n_dn-1)/2
@@ -245,8 +246,8 @@ void launch_filters(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r,
 }
 
 template void launch_filters<double>(const pn_ctx*, hipStream_t, int64_t, const double*, const double*, char*,
-                                     const WsLayout&, bool);
+                                     const WsLayout&);
 template void launch_filters<float>(const pn_ctx*, hipStream_t, int64_t, const double*, const float*, char*,
-                                    const WsLayout&, bool);
+                                    const WsLayout&);
 
 }  // namespace pn

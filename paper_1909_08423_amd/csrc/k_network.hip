@@ -28,7 +28,7 @@ struct HOut {
   int ld, rows, DZ;
   RowDiv N;
   const TN* b;
-  TN* hval;       // [walker][L][N][DZ] at this layer and the block's first walker
+  TN* hval;       // h table at this layer and the block's first walker
   int64_t wstep;  // its walker stride
   template <typename A>
   __device__ void operator()(int, int, A&) const {}
@@ -113,7 +113,7 @@ struct FOut {
 // with the same sums in the same order.
 template <typename TN, int ZCH>
 __global__ __launch_bounds__(kThreads, sizeof(TN) == 4 ? 3 : 2) void k_net_value(
-    Dims d, DevTables t, int64_t nw, int WPB, const TN* __restrict__ P, ParamLayout pl, const TN* __restrict__ filt,
+    Dims d, DevTables t, int64_t nw, int WPB, const TN* __restrict__ P, ParamLayout pl, int jets, const TN* __restrict__ filt,
     TN* __restrict__ hval, TN* __restrict__ kcoef, TN* __restrict__ ecoef, double* __restrict__ fval,
     double* __restrict__ jval, TN* __restrict__ xval) {
   extern __shared__ __align__(16) char smem[];
@@ -128,8 +128,10 @@ __global__ __launch_bounds__(kThreads, sizeof(TN) == 4 ? 3 : 2) void k_net_value
   TN* H = X + WPB * N * LDX;                                 // [WPB*N][LDW] h, later the backflow head
   TN* Z = H + WPB * N * LDW;                                 // [ZCH][WPB*N][LDZ] messages
   TN* E = Z + ZCH * WPB * N * LDZ;                           // [2][WPB][LDX] Jastrow head
-  const int64_t fl_stride = (int64_t)3 * d.n_pairs * DZ;  // per layer
+  const int64_t fl_stride = (int64_t)jets * d.n_pairs * DZ;  // per layer
   const int64_t fw_stride = fl_stride * d.L;               // per walker
+  // the tangent pass takes h walker by walker, the value-path adjoint layer by layer
+  const int64_t h_walker = jets == 1 ? 1 : d.L, h_layer = jets == 1 ? nw : 1;
   const int ZS = WPB * N * LDZ;
   const int sx = log2_of(DX), sz = log2_of(DZ);
   const RowDiv rN(N);
@@ -147,8 +149,8 @@ __global__ __launch_bounds__(kThreads, sizeof(TN) == 4 ? 3 : 2) void k_net_value
     const ParamLayout::Layer& Lp = pl.layer[n];
     if (xval) save_x(n);
     gemm_mfma<TN, false, HOut<TN>>(X, LDX, R, DX, P + Lp.hW, DZ, H, LDW, false, false,
-                                   HOut<TN>{H, LDW, R, DZ, rN, P + Lp.hb, hval + (w0 * d.L + n) * N * DZ,
-                                            (int64_t)d.L * N * DZ});
+                                   HOut<TN>{H, LDW, R, DZ, rN, P + Lp.hb, hval + (w0 * h_walker + n * h_layer) * N * DZ,
+                                            h_walker * N * DZ});
     __syncthreads();
     for (int ch0 = 0; ch0 < 3; ch0 += ZCH) {
       for (int q = threadIdx.x; q < ZCH * R * DZ; q += blockDim.x) {
@@ -284,7 +286,7 @@ void launch_net_value(const pn_ctx* c, hipStream_t s, int64_t nw, const TN* P, c
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)L.lds_value);
   hipLaunchKernelGGL(kern, dim3((unsigned)nb), dim3(kThreads), L.lds_value, s, d, c->t, nw, L.wpb_value,
-                     P, c->pl, reinterpret_cast<const TN*>(ws + L.filt), reinterpret_cast<TN*>(ws + L.hval),
+                     P, c->pl, L.jets, reinterpret_cast<const TN*>(ws + L.filt), reinterpret_cast<TN*>(ws + L.hval),
                      reinterpret_cast<TN*>(ws + L.kcoef), reinterpret_cast<TN*>(ws + L.ecoef),
                      reinterpret_cast<double*>(ws + L.fval), reinterpret_cast<double*>(ws + L.jval),
                      L.xval ? reinterpret_cast<TN*>(ws + L.xval) : nullptr);

@@ -29,13 +29,19 @@ template <typename TN>
 size_t tangent_adj_ops_bytes(const Dims& d, int T, int64_t nw);
 template <typename TN>
 size_t tangent_adj_lds_bytes(const Dims& d, int T, bool global_arena);
-size_t backward_scratch_bytes(const pn_ctx* c, int64_t tile, bool fp32);
+size_t backward_scratch_bytes(const pn_ctx* c, int64_t tile, bool fp32, bool full);
 bool backward_supported(const pn_ctx* c, bool fp32);
 
 namespace {
 
 constexpr size_t kAlign = 256;
-constexpr size_t kWsBudget = size_t(6) << 30;  // walker tiles keep the workspace below ~6 GiB
+// Walker tiles are sized so that the regions of per_walker (those of the
+// forward pass, and what the adjoints keep of it) stay below 6 GiB.  The tile is
+// part of the FP32 rounding of a gradient, so the adjoints' own scratch does not
+// shrink it: gradient slots, filter cotangents and row tables come on top (9.6
+// GiB in all at the most, 12.1 for the full adjoint, over 1400 plans of 1 to 48
+// electrons and up to 300000 walkers).
+constexpr size_t kWsBudget = size_t(6) << 30;
 constexpr size_t kLdsMax = 160 * 1024;
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
@@ -302,7 +308,8 @@ WsLayout plan(const pn_ctx* c, int64_t nw, pn_precision prec, int mode, size_t b
   L.params_net = region(fp64 ? 0 : (size_t)c->pl.total * sizeof(float));
   L.geo = region((size_t)tile * kGeoStride(N) * 8);
   L.phi = region((size_t)tile * N * M * 7 * 8);
-  L.filt = region((size_t)tile * d.L * 3 * d.n_pairs * d.DZ * tn);
+  L.jets = tangents ? 3 : 1;
+  L.filt = region((size_t)tile * d.L * L.jets * d.n_pairs * d.DZ * tn);
   L.hval = region((size_t)tile * d.L * N * d.DZ * tn);
   L.kcoef = region((size_t)tile * 4 * N * d.DX * tn);
   L.ecoef = region((size_t)tile * 4 * d.DX * tn);
@@ -321,7 +328,11 @@ WsLayout plan(const pn_ctx* c, int64_t nw, pn_precision prec, int mode, size_t b
   L.gpart = 0;
   if (backward) {
     L.xval = region((size_t)tile * (d.L + 1) * N * d.DX * tn);
-    L.gpart = region(backward_scratch_bytes(c, tile, !fp64));
+    // the nucleus values' gradient keeps its slots here too; the full adjoint's
+    // tables are read before the value-path adjoint's scratch is written
+    size_t bytes = std::max(backward_scratch_bytes(c, tile, !fp64, full), cusp_grad_slot_bytes(d, tile));
+    if (full) bytes = std::max(bytes, fp64 ? tangent_adj_ops_bytes<double>(d, L.T, tile) : tangent_adj_ops_bytes<float>(d, L.T, tile));
+    L.gpart = L.tanops = region(bytes);
   }
   if (L.lowrank) {
     L.g0 = region((size_t)tile * gsz * 8);
@@ -347,8 +358,7 @@ WsLayout plan(const pn_ctx* c, int64_t nw, pn_precision prec, int mode, size_t b
     L.ctkc = region((size_t)tile * 4 * N * d.DX * tn);
     L.ctec = region((size_t)tile * 4 * d.DX * tn);
     L.ct0 = region((size_t)tile * 8);
-    L.tslot = region((size_t)kSlotsTanAdj * c->pl.total * tn);
-    L.tanops = region(fp64 ? tangent_adj_ops_bytes<double>(d, L.T, tile) : tangent_adj_ops_bytes<float>(d, L.T, tile));
+    L.tslot = region((size_t)std::min<int64_t>(tile, kSlotsTanAdj) * c->pl.total * tn);
   }
   L.total = off;
   return L;
@@ -909,14 +919,14 @@ pn_status eval_impl(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r,
       launch_fill(s, n, reinterpret_cast<double*>(base + L.jval), 0.0);
     } else if (fp64) {
       clk.begin(2);
-      launch_filters<double>(c, s, n, rt, static_cast<const double*>(P), base, L, derivs);
+      launch_filters<double>(c, s, n, rt, static_cast<const double*>(P), base, L);
       clk.end(2);
       clk.begin(3);
       launch_net_value<double>(c, s, n, static_cast<const double*>(P), base, L);
       clk.end(3);
     } else {
       clk.begin(2);
-      launch_filters<float>(c, s, n, rt, static_cast<const float*>(P), base, L, derivs);
+      launch_filters<float>(c, s, n, rt, static_cast<const float*>(P), base, L);
       clk.end(2);
       clk.begin(3);
       launch_net_value<float>(c, s, n, static_cast<const float*>(P), base, L);
@@ -992,10 +1002,10 @@ pn_status pn_eval_backward(const pn_ctx* c, hipStream_t s, int64_t nw, const dou
     const double* rt = r + w0 * d.N * 3;
     launch_geometry_orbitals(c, s, n, rt, base, L, full);
     if (fp64) {
-      launch_filters<double>(c, s, n, rt, static_cast<const double*>(P), base, L, full);
+      launch_filters<double>(c, s, n, rt, static_cast<const double*>(P), base, L);
       launch_net_value<double>(c, s, n, static_cast<const double*>(P), base, L);
     } else {
-      launch_filters<float>(c, s, n, rt, static_cast<const float*>(P), base, L, full);
+      launch_filters<float>(c, s, n, rt, static_cast<const float*>(P), base, L);
       launch_net_value<float>(c, s, n, static_cast<const float*>(P), base, L);
     }
     launch_slater_value(c, s, n, base, L, la, sg);
@@ -1059,10 +1069,10 @@ pn_status pn_eval_backward_cusp(const pn_ctx* c, hipStream_t s, int64_t nw, cons
       launch_fill(s, n * d.N * d.M, reinterpret_cast<double*>(base + L.fval), 1.0);
       launch_fill(s, n, reinterpret_cast<double*>(base + L.jval), 0.0);
     } else if (fp64) {
-      launch_filters<double>(c, s, n, rt, static_cast<const double*>(P), base, L, false);
+      launch_filters<double>(c, s, n, rt, static_cast<const double*>(P), base, L);
       launch_net_value<double>(c, s, n, static_cast<const double*>(P), base, L);
     } else {
-      launch_filters<float>(c, s, n, rt, static_cast<const float*>(P), base, L, false);
+      launch_filters<float>(c, s, n, rt, static_cast<const float*>(P), base, L);
       launch_net_value<float>(c, s, n, static_cast<const float*>(P), base, L);
     }
     launch_slater_value(c, s, n, base, L, la, sg);

@@ -100,12 +100,13 @@ struct WsLayout {
   size_t lds_filter;
   int filt_rows;       // pairs per block in the filter kernel
   bool stage_filters;  // tangent pass copies the layer's filter tables to LDS
+  int jets;            // jets of the filter table: w, w'/d, w'' where the tangent pass reads them, else w alone
   // offsets
   size_t params_net;   // converted params (float) when the network is FP32/BF16
   size_t geo;          // [tile][GEO] V, gamma, then per electron grad(3) + hess diag(3)
   size_t phi;          // [tile][N][M][7] value, grad(3), d2 diag(3)
-  size_t filt;         // [tile][L][3][n_pairs][DZ]  (w, w'/d, w'')  net type
-  size_t hval;         // [tile][L][N][DZ]                           net type
+  size_t filt;         // [tile][L][jets][n_pairs][DZ]  net type
+  size_t hval;         // [tile][L][N][DZ], one jet: [L][walkers of the launch][N][DZ]  net type
   size_t kcoef;        // [tile][2][2][N][DX] (ssp', ssp'') per kappa hidden layer
   size_t ecoef;        // [tile][2][2][DX]
   size_t fval;         // [tile][N][M]  double
@@ -118,8 +119,8 @@ struct WsLayout {
   size_t jtan;         // [tile][n_chunks][T+1] double
   size_t partial;      // [tile][n_chunks][2]
   size_t xval;         // [L+1][walkers of the launch][N][DX] activations (backward only)
-  size_t adj;          // backward scratch
-  size_t gpart;        // [n_blocks][n_params] per-block parameter gradients
+  size_t adj;          // [tile][max(3N, 2)] gradient of calls that want none, or ln|psi| and sign
+  size_t gpart;        // scratch of the value-path adjoint: gradient slots, filter cotangents, row tables
   // full adjoint (cotangents on grad / lap / E_loc)
   bool full;
   size_t lds_tadj;     // bytes of the full adjoint's chunk rule
@@ -138,8 +139,8 @@ struct WsLayout {
   size_t ctkc;         // [tile][2][2][N][DX]    net type
   size_t ctec;         // [tile][2][2][DX]       net type
   size_t ct0;          // [tile] zeros (absent ln|psi| cotangent)
-  size_t tslot;        // [kSlotsTanAdj][n_params] net type
-  size_t tanops;       // tables of one batch of walkers of the tangent adjoint
+  size_t tslot;        // [at most kSlotsTanAdj][n_params] net type
+  size_t tanops;       // tables of one batch of walkers of the tangent adjoint (in gpart, which is used after them)
   // low-rank determinant path (forward only)
   bool lowrank;
   size_t lds_lr;       // dynamic LDS of the low-rank tangent kernel
@@ -152,7 +153,7 @@ struct WsLayout {
   size_t total;
 };
 
-constexpr int kSlotsTanAdj = 512;  // gradient slots of the tangent adjoint
+constexpr int kSlotsTanAdj = 512;  // gradient slots of the tangent adjoint, at most
 
 constexpr int kGeoStride(int N) { return 4 + 6 * N; }  // V, gamma, lap_gamma, pad, N*(grad3, hess3)
 
@@ -232,7 +233,7 @@ void launch_geometry_orbitals(const pn_ctx* c, hipStream_t s, int64_t nw, const 
                               const WsLayout& L, bool derivs);
 template <typename TN>
 void launch_filters(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r, const TN* P, char* ws,
-                    const WsLayout& L, bool jets);
+                    const WsLayout& L);
 template <typename TN>
 void launch_net_value(const pn_ctx* c, hipStream_t s, int64_t nw, const TN* P, char* ws, const WsLayout& L);
 template <typename TN>
@@ -257,6 +258,7 @@ void launch_convert_params(hipStream_t s, int64_t n, const double* src, float* d
 void launch_fill0(hipStream_t s, int64_t n, double* dst);
 void launch_fill(hipStream_t s, int64_t n, double* dst, double v);
 size_t cusp_grad_lds_bytes(const Dims& d);
+size_t cusp_grad_slot_bytes(const Dims& d, int64_t nw);
 void launch_cusp_grad(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r, char* ws, const WsLayout& L,
                       const double* ct, double* slot, double* grad);
 void launch_adj_det(const pn_ctx* c, hipStream_t s, int64_t nw, const WsLayout& L, char* ws, const double* ct_logabs,

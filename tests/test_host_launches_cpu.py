@@ -80,3 +80,27 @@ def test_full_adjoint_of_many_walkers(run):
              for nw in (65536, 65537, 300000) for prec in (FP64, FP32)]
     for call, (status, launches, beyond) in zip(calls, run(calls)):
         assert status == OK and launches > 0 and not beyond, (call, beyond)
+
+
+# value-path adjoint and VMC step of the form that added each group's weight
+# gradients to slots in memory and kept no row tables: what callers with a
+# fixed budget of memory (admission of serving jobs) have counted on
+FORMER_BYTES = [
+    ([1, 1, 2, 8, 4], [16, 32, 16, 2, 0], 8192, FP64, 152212480, 153063680),
+    ([1, 1, 2, 8, 4], [16, 32, 16, 2, 0], 8192, FP32, 82053888, 82905088),
+    ([2, 2, 1, 14, 16], [32, 64, 32, 3, 0], 1024, FP32, 179078400, 179717632),
+    ([4, 3, 7, 16, 9], [32, 64, 32, 3, 0], 8192, FP64, 2432308224, 2434543360),
+    ([5, 5, 1, 16, 16], [32, 64, 32, 3, 0], 4096, FP32, 670652160, 672312320),
+    ([5, 5, 1, 16, 16], [32, 64, 32, 3, 0], 16384, FP64, 4187689984, 4192839936),
+    ([5, 5, 10, 13, 10], [32, 64, 32, 3, 0], 8192, FP32, 2289713152, 2292537344),
+    ([9, 9, 1, 26, 16], [32, 64, 32, 3, 0], 4096, FP64, 3030365184, 3043437056),
+    ([15, 15, 2, 23, 64], [32, 128, 64, 4, 0], 256, FP32, 1280890112, 1283305984),
+    ([15, 15, 2, 23, 64], [32, 128, 64, 4, 0], 16384, FP32, 8741715456, 8756453120),
+    ([24, 24, 2, 31, 4], [16, 128, 64, 2, 0], 512, FP64, 3680461824, 3887816192),
+]
+
+
+def test_workspaces_have_not_grown(run):
+    rows = run([[*row[:4], "bytes"] for row in FORMER_BYTES])
+    for (*call, adjoint, vmc), (now_adjoint, _, now_vmc, _) in zip(FORMER_BYTES, rows):
+        assert now_adjoint <= adjoint and now_vmc <= vmc, (call, now_adjoint / adjoint, now_vmc / vmc)
