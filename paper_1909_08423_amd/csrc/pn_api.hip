@@ -373,6 +373,12 @@ static bool no_network(const Dims& d) {
 // asks before it enqueues anything).
 static bool value_pass_fits(const Dims& d, const WsLayout& L) { return no_network(d) || L.lds_value <= kLdsMax; }
 
+// Its derivative pass does.  Every such call launches the member-by-member
+// determinant tangents: on all walkers, or on those the low-rank path hands back.
+static bool tangents_fit(const Dims& d, const WsLayout& L) {
+  return L.lds_tangent <= kLdsMax && slater_tangent_lds_bytes(d, L.T) <= kLdsMax;
+}
+
 // ---- optional stage timing ----
 namespace {
 void harvest_set(pn_ctx::Timing* T, int set) {
@@ -866,9 +872,11 @@ pn_status pn_eval(const pn_ctx* c, hipStream_t s, int64_t nw, const double* r, c
   if (!c || nw < 0 || prec < PN_PREC_FP64 || prec > PN_PREC_NET_BF16) return PN_ERR_INVALID_ARG;
   if (nw == 0) return PN_OK;
   if (!r || !params || !logabs || !sign || !ws) return PN_ERR_INVALID_ARG;
-  WsLayout L = plan(c, nw, prec, (grad || lap || eloc) ? kPlanForward : kPlanValueOnly);
+  const bool derivs = grad || lap || eloc;
+  WsLayout L = plan(c, nw, prec, derivs ? kPlanForward : kPlanValueOnly);
   if (ws_bytes < L.total) return PN_ERR_WORKSPACE_TOO_SMALL;
-  if (L.lds_tangent > kLdsMax || !value_pass_fits(c->d, L)) return PN_ERR_UNSUPPORTED_SHAPE;
+  if (L.lds_tangent > kLdsMax || !value_pass_fits(c->d, L) || (derivs && !tangents_fit(c->d, L)))
+    return PN_ERR_UNSUPPORTED_SHAPE;
   return eval_impl(c, s, nw, r, params, prec, logabs, sign, grad, lap, eloc, static_cast<char*>(ws), L);
 }
 
@@ -880,9 +888,11 @@ pn_status pn_eval_noalloc(const pn_ctx* c, hipStream_t s, int64_t nw, const doub
   char* base = static_cast<char*>(scratch_of(c->device));
   if (!base) return PN_ERR_DEVICE;
   // walker tiles sized for the static scratch (down to one walker)
-  WsLayout L = plan(c, nw, prec, (grad || lap || eloc) ? kPlanForward : kPlanValueOnly, kScratchBytes, 1);
+  const bool derivs = grad || lap || eloc;
+  WsLayout L = plan(c, nw, prec, derivs ? kPlanForward : kPlanValueOnly, kScratchBytes, 1);
   if (L.total > kScratchBytes) return PN_ERR_WORKSPACE_TOO_SMALL;
-  if (L.lds_tangent > kLdsMax || !value_pass_fits(c->d, L)) return PN_ERR_UNSUPPORTED_SHAPE;
+  if (L.lds_tangent > kLdsMax || !value_pass_fits(c->d, L) || (derivs && !tangents_fit(c->d, L)))
+    return PN_ERR_UNSUPPORTED_SHAPE;
   return eval_impl(c, s, nw, r, params, prec, logabs, sign, grad, lap, eloc, base, L);
 }
 
@@ -984,7 +994,7 @@ pn_status pn_eval_backward(const pn_ctx* c, hipStream_t s, int64_t nw, const dou
   if (ws_bytes < L.total) return PN_ERR_WORKSPACE_TOO_SMALL;
   const Dims& d = c->d;
   if (!value_pass_fits(d, L)) return PN_ERR_UNSUPPORTED_SHAPE;
-  if (full && (L.lds_tadj > kLdsMax || L.lds_adjdet > kLdsMax || L.lds_tangent > kLdsMax ||
+  if (full && (L.lds_tadj > kLdsMax || L.lds_adjdet > kLdsMax || !tangents_fit(d, L) ||
                backward_filter_lds_bytes(d, !fp64, true) > kLdsMax))
     return PN_ERR_UNSUPPORTED_SHAPE;
   char* base = static_cast<char*>(ws);

@@ -82,6 +82,18 @@ def test_full_adjoint_of_many_walkers(run):
         assert status == OK and launches > 0 and not beyond, (call, beyond)
 
 
+def test_refused_calls_enqueue_nothing(run):
+    """The largest tables: as many orbitals as the network takes, many members."""
+    calls = [[[(n + 1) // 2, n // 2, 2, dx, n_det], [k, dx, dz, 2, flags], 8, prec, kind]
+             for n in (2, 7, 16, 31, 40, 47, 52, 58, 64) for dx, dz in widths() if (n + 1) // 2 <= dx
+             for n_det, k, flags in ((1, 64, 0), (64, 16, 0), (64, 32, 4), (5, 16, 3))
+             for prec in (FP64, FP32, pn.PN_PREC_NET_BF16)
+             for kind in ("value", "eval", "noalloc", "adjoint", "full", "cusp")]
+    for call, (status, launches, beyond) in zip(calls, run(calls)):
+        assert not beyond, (call, beyond[0])
+        assert status == OK or launches == 0, (call, status)
+
+
 # value-path adjoint and VMC step of the form that added each group's weight
 # gradients to slots in memory and kept no row tables: what callers with a
 # fixed budget of memory (admission of serving jobs) have counted on
