@@ -321,6 +321,7 @@ pn_status check_job(const pn_ctx* c, const pn_vmc_job* job, pn_precision prec, c
   if (!job->r || !job->params || !job->adam_m || !job->adam_v || !job->eloc || !job->stats || job->step < 0)
     return PN_ERR_INVALID_ARG;
   if (!(hp->sigma > 0) || !(hp->t0 > 0) || !(hp->clip_q > 0)) return PN_ERR_INVALID_ARG;
+  if (!c->vmc_fits[prec]) return PN_ERR_UNSUPPORTED_SHAPE;
   if (ws_bytes < vmc_layout(c, B, prec).total) return PN_ERR_WORKSPACE_TOO_SMALL;
   return PN_OK;
 }

@@ -749,6 +749,11 @@ pn_status pn_ctx_create(const pn_system_desc* sys, const pn_net_desc* net, pn_ct
     pn_ctx_destroy(c);
     return PN_ERR_DEVICE;
   }
+  for (pn_precision prec : {PN_PREC_FP64, PN_PREC_NET_FP32, PN_PREC_NET_BF16}) {
+    const WsLayout L = plan(c, 1, prec, kPlanForward);
+    c->vmc_fits[prec] = value_pass_fits(d, L) && tangents_fit(d, L) &&
+                        (no_network(d) || backward_supported(c, prec != PN_PREC_FP64));
+  }
   *out = c;
   return PN_OK;
 }

@@ -184,6 +184,7 @@ struct pn_ctx {
   };
   mutable Timing* timing = nullptr;
   int lr_kmax = 0;  // most orbitals of a spin that a determinant replaces (low-rank path)
+  bool vmc_fits[3] = {};  // per precision: no part of a VMC step refuses this shape (whatever the walkers)
 };
 
 namespace pn {

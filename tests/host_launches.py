@@ -69,6 +69,9 @@ def main():
                             m.vmc_workspace_bytes(ctx, min(nw, 16384), prec),
                             ctx.plan(nw, prec, m.PLAN_EVAL)["workspace_bytes"]])
             continue
+        job = m.pn_vmc_job(nw, *[p] * 6, 1, 0)
+        slot = m.pn_job_slot(c, job, p, big.value)
+        hp = m.pn_vmc_hparams(*m.DEFAULT_HPARAMS.values())
         fake.fake_reset()
         st = {
             "value": lambda: lib.pn_eval(c, none, nw, p, p, prec, p, p, none, none, none, p, big),
@@ -76,6 +79,10 @@ def main():
             "noalloc": lambda: lib.pn_eval_noalloc(c, none, nw, p, p, prec, p, p, p, p, p),
             "adjoint": lambda: lib.pn_eval_backward(c, none, nw, p, p, prec, p, none, none, none, p, p, big),
             "full": lambda: lib.pn_eval_backward(c, none, nw, p, p, prec, p, p, p, none, p, p, big),
+            "vmc": lambda: lib.pn_vmc_step(c, none, ctypes.byref(job), prec, ctypes.byref(hp), p, big),
+            "serve": lambda: lib.pn_serve_step(none, ctypes.byref(slot), 1, prec, ctypes.byref(hp)),
+            "langevin": lambda: lib.pn_langevin_run(c, none, nw, p, p, prec,
+                                                    ctypes.byref(m.pn_langevin_hparams(0.57, 1.0)), p, 2, 1, 0, p, p, big),
             "cusp": lambda: lib.pn_eval_backward_cusp(c, none, nw, p, p, prec, p, p, p, big),
         }[kind]()
         beyond = []

@@ -94,6 +94,23 @@ def test_refused_calls_enqueue_nothing(run):
         assert status == OK or launches == 0, (call, status)
 
 
+def test_refused_steps_enqueue_nothing(run):
+    """A VMC or Langevin step is all of its evaluations and its adjoint, or nothing."""
+    shapes = [[[(n + 1) // 2, n // 2, 2, dx, 5], [k, dx, dz, 2, flags]]
+              for n in (2, 16, 31, 47, 64) for dx, dz in widths() if (n + 1) // 2 <= dx
+              for k, flags in ((16, 0), (64, 0), (16, 3))]
+    parts, steps = ("value", "eval", "adjoint"), ("vmc", "serve", "langevin")
+    for prec in (FP64, FP32, pn.PN_PREC_NET_BF16):
+        rows = run([[*s, 8, prec, kind] for s in shapes for kind in parts + steps])
+        for k, s in enumerate(shapes):
+            value, evaluation, adjoint, vmc, serve, langevin = rows[6 * k:6 * k + 6]
+            for status, launches, beyond in (vmc, serve, langevin):
+                assert not beyond and (status == OK) == (launches > 0), (s, prec, status, launches)
+            whole = value[0] == evaluation[0] == adjoint[0] == OK
+            assert (vmc[0] == OK) == (serve[0] == OK) == whole, (s, prec)
+            assert (langevin[0] == OK) == (evaluation[0] == OK), (s, prec)
+
+
 # value-path adjoint and VMC step of the form that added each group's weight
 # gradients to slots in memory and kept no row tables: what callers with a
 # fixed budget of memory (admission of serving jobs) have counted on
