@@ -38,7 +38,8 @@
  *  - Limits: n_up, n_down <= 32; n_elec <= 64; n_det <= 64; n_nuc <= 64;
  *    n_feat, dim_x and dim_z each one of 16, 32, 64, 128; n_mo <= dim_x;
  *    n_layers <= 8; shells are s (l = 0) or p (l = 1).  Anything else
- *    returns PN_ERR_UNSUPPORTED_SHAPE.
+ *    returns PN_ERR_UNSUPPORTED_SHAPE, and so does a call of which one
+ *    walker's tables exceed a workgroup's LDS (160 KB).
  */
 #ifndef PAULINET_H
 #define PAULINET_H

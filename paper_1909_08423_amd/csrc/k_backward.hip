@@ -844,7 +844,7 @@ static int bwd_wb(const Dims& d) {
 }
 
 // k_bwd_net keeps its union region in a global arena when the whole block
-// does not fit in LDS (64 electrons of width 128 in FP64)
+// does not fit in LDS (40 electrons of width 128 in FP64)
 template <typename TN>
 static bool bwd_net_arena(const Dims& d) {
   return bwd_net_lds<TN>(d, bwd_wb<TN>(d)) > 160 * 1024;

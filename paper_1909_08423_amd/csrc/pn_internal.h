@@ -208,9 +208,10 @@ __device__ __forceinline__ float ssp(float x) {
 }
 
 // Index arithmetic without divisions (a division by a run-time value is some
-// 25 vector instructions): widths are powers of two, and a row index below
-// 2^14 is divided by N <= 64 through the reciprocal ceil(2^20 / N), whose
-// product with it stays below 2^31 and is off by less than 1 / N.
+// 25 vector instructions): widths are powers of two, and a row index is
+// divided by N <= 64 through the reciprocal ceil(2^20 / N).  Exact for rows
+// below 4096 (the product stays below 2^32 and the quotient is off by less than
+// 1 / N); the row tables of a block have some tens of rows.
 struct RowDiv {
   int N, m;
   __device__ explicit RowDiv(int n) : N(n), m(((1 << 20) + n - 1) / n) {}
